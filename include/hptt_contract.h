@@ -91,7 +91,11 @@ hptt_status_t hptt_contraction_describe(hptt_contraction_t plan, char *buf, size
 /*
  * Queue the contraction on `stream`: transpositions of A and B into the
  * workspace where the plan needs them, the GEMM, the transposition of the
- * product into C where needed.  A, B, C and workspace are device pointers;
+ * product into C where needed -- or, where the plan needs transpositions and
+ * that is estimated faster (few contracted elements; hptt_contraction_describe
+ * ends in "direct"), one kernel that reads A and B and writes C where they
+ * lie and leaves the workspace alone.  The workspace's size is checked either
+ * way.  A, B, C and workspace are device pointers;
  * workspace must hold workspace_bytes (256-byte aligned, may be NULL when
  * that is 0) and overlap none of A, B, C.  Returns HPTT_ERROR_INVALID_ARGUMENT
  * for a NULL tensor or a missing or short workspace, HPTT_ERROR_HIP when a

@@ -22,7 +22,7 @@ LIB = os.path.join(PKG, "libhptt.so")
 # Contractions (transposition - GEMM - transposition) link rocBLAS, so they
 # live in a library of their own on top of libhptt.so.
 CONTRACT_LIB = os.path.join(PKG, "libhptt_contract.so")
-CONTRACT_SOURCES = ["contract.hip"]
+CONTRACT_SOURCES = ["contract.hip", "contract_direct.hip", "contract_direct_plan.cpp"]
 
 ARCH = "gfx950"
 # the tile kernel instantiations are split over six files so they compile in parallel

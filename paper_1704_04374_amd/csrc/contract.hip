@@ -1,5 +1,6 @@
 // Tensor contractions as transposition - GEMM - transposition (Section 1;
-// the contraction experiment of Section 4.1).  The plan groups the modes
+// the contraction experiment of Section 4.1), or in one pass where that is
+// estimated faster (contract_direct.h).  The plan groups the modes
 // into the rows (X), columns (Y), contracted (K) and batch (L) modes of one
 // column-major strided-batched GEMM, C'[X,Y,L] = P[X,K,L] . Q[K,Y,L], and
 // searches the mode orders and the role of A and B (P = A, Q = B, or the
@@ -15,6 +16,7 @@
 #include <string>
 #include <vector>
 
+#include "contract_direct.h"
 #include "hptt_contract.h"
 
 namespace {
@@ -77,6 +79,10 @@ struct hptt_contraction_s {
     std::string ma, mb, mc;
     int64_t ext[256];
     Choice ch;
+    // the direct kernel, where it takes the plan's place (use_direct)
+    bool direct = false;
+    int directSwap = 0;  // 0: P = A, Q = B; 1: P = B, Q = A
+    hptt::DirectArgs dargs;
     hptt_plan_t planP = nullptr, planQ = nullptr, planC = nullptr;
     int64_t offP = 0, offQ = 0, offC = 0, wsBytes = 0;
     rocblas_handle handle = nullptr;
@@ -103,6 +109,60 @@ hptt_status_t make_transpose(const std::string& from, const std::string& to, con
     permutation(from, to, perm);
     for (int d = 0; d < n; ++d) size[d] = ext[static_cast<unsigned char>(from[d])];
     return hptt_create_plan(plan, perm, n, size, alpha, beta, dtype);
+}
+
+// Whether the direct kernel takes the place of transposition - GEMM -
+// transposition; fills p->dargs.  A plan without transpositions is a plain
+// GEMM and stays one, and so does alpha = 0, for which a GEMM reads neither
+// operand.  Otherwise the estimate of each decides: the direct kernel saves
+// the transposed operands' and product's round trips (MI355X, fp64: abcde =
+// efbad.cf, 32 contracted elements, 243 -> 78 us; abcd = ebad.ce 127 -> 48;
+// fp32 abcd = dbea.ec, 64 contracted, 246 -> 86), the library GEMM has nearly
+// twice its arithmetic rate (ab = acd.dbc, 4096 contracted: 594 us against 841).
+bool use_direct(hptt_contraction_s* p) {
+    const bool zero = p->dtype == HPTT_FLOAT32 ? float(p->alpha) == 0.f : p->alpha == 0.0;
+    const hptt_contraction_info_t& in = p->info;
+    const int transposes = in.transpose_a + in.transpose_b + in.transpose_c;
+    if (zero || transposes == 0) return false;
+    const int elem = p->dtype == HPTT_FLOAT32 ? 4 : 8;
+    for (int swap = 0; swap < 2; ++swap)
+        if (hptt::plan_direct(swap ? p->mb : p->ma, swap ? p->ma : p->mb, p->mc, p->ext, elem,
+                              &p->dargs)) {
+            p->directSwap = swap;
+            return hptt::direct_us(p->dargs, elem) <
+                   hptt::transposed_us(p->dargs, elem, transposes, in.bytes_transposed);
+        }
+    return false;
+}
+
+bool disjoint(const void* a, int64_t na, const void* b, int64_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x + uintptr_t(na) <= y || y + uintptr_t(nb) <= x;
+}
+
+// Whether this call's tensors allow the direct kernel: it reads A and B while
+// it writes C.  Overlapping or misaligned tensors keep the transpositions,
+// which copy an overlapping operand first or refuse the call.
+bool direct_call(const hptt_contraction_s* p, const void* A, const void* B, const void* C,
+                 const void* ws) {
+    if (!p->direct) return false;
+    const int64_t elem = p->dtype == HPTT_FLOAT32 ? 4 : 8;
+    const int64_t nA = volume(p->ma, p->ext) * elem, nB = volume(p->mb, p->ext) * elem,
+                  nC = volume(p->mc, p->ext) * elem;
+    for (const void* t : {A, B, C})
+        if (reinterpret_cast<uintptr_t>(t) % uintptr_t(elem)) return false;
+    return disjoint(C, nC, A, nA) && disjoint(C, nC, B, nB) && disjoint(ws, p->wsBytes, A, nA) &&
+           disjoint(ws, p->wsBytes, B, nB) && disjoint(ws, p->wsBytes, C, nC);
+}
+
+hptt_status_t run_direct(const hptt_contraction_s* p, const void* A, const void* B, void* C,
+                         hipStream_t stream) {
+    hipError_t err = hipSuccess;
+    const bool ok = hptt::launch_direct(p->dargs, p->dtype == HPTT_FLOAT64, p->directSwap ? B : A,
+                                        p->directSwap ? A : B, C, p->alpha, p->beta, stream, &err);
+    if (ok) return HPTT_SUCCESS;
+    hptt::record_hip_error(err);
+    return HPTT_ERROR_HIP;
 }
 
 int64_t align_up(int64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -247,6 +307,7 @@ hptt_status_t hptt_contraction_create(hptt_contraction_t* planOut, hptt_dtype_t 
         in.bytes_transposed = double(elem) * ((c.tP ? 2 * vP : 0) + (c.tQ ? 2 * vQ : 0) +
                                               (c.tC ? (beta != 0 ? 3 : 2) * vC : 0));
     }
+    p->direct = use_direct(p);
     char buf[512];
     snprintf(buf, sizeof(buf),
              "contraction %s=%s*%s dtype=%s gemm=%s%s m=%lld(%s) n=%lld(%s) k=%lld(%s) "
@@ -258,6 +319,7 @@ hptt_status_t hptt_contraction_create(hptt_contraction_t* planOut, hptt_dtype_t 
              (long long)ws);
     p->desc = buf;
     if (c.swap) p->desc += " (as C^T = B^T A^T)";
+    if (p->direct) p->desc += " direct";
     *planOut = p;
     return HPTT_SUCCESS;
 }
@@ -349,6 +411,7 @@ hptt_status_t hptt_contraction_exec(hptt_contraction_t p, const void* A, const v
     if (p->wsBytes > 0 && (!workspace || workspaceBytes < size_t(p->wsBytes) ||
                            reinterpret_cast<uintptr_t>(workspace) % kAlign))
         return HPTT_ERROR_INVALID_ARGUMENT;
+    if (direct_call(p, A, B, C, workspace)) return run_direct(p, A, B, C, stream);
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return HPTT_ERROR_HIP;
     if (!p->handle || p->handleDevice != device) {
@@ -443,6 +506,7 @@ hptt_status_t hptt_contraction_exec_no_alloc(hptt_contraction_t p, const void* A
         return HPTT_ERROR_HIP;
     }
     if (need > size_t(HPTT_CONTRACTION_STATIC_BLAS_BYTES)) return HPTT_ERROR_UNSUPPORTED;
+    if (direct_call(p, A, B, C, dev.base)) return run_direct(p, A, B, C, stream);
     return run(p, A, B, C, dev.base, dev.handle, stream);
 }
 

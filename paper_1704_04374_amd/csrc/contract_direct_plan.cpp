@@ -1,0 +1,201 @@
+// Planner of the direct contraction kernel (contract_direct.h): host code
+// only, no HIP call.
+#include <string.h>
+
+#include "contract_direct.h"
+
+namespace hptt {
+
+namespace {
+
+constexpr int64_t kLimit = int64_t(1) << 31;
+
+int64_t stride_of(const std::string& modes, char m, const int64_t* ext) {
+    int64_t s = 1;
+    for (char c : modes) {
+        if (c == m) return s;
+        s *= ext[static_cast<unsigned char>(c)];
+    }
+    return 0;
+}
+
+bool has(const std::string& s, char c) { return s.find(c) != std::string::npos; }
+
+int ceil_log2(int64_t v) {
+    int l = 0;
+    while ((int64_t(1) << l) < v) ++l;
+    return l;
+}
+
+void set_group(ModeGroup& g, const std::string& modes, const std::string& t0,
+               const std::string& t1, const int64_t* ext, int elem) {
+    g.n = 0;
+    int64_t total = 1;
+    for (char c : modes) {
+        const int64_t e = ext[static_cast<unsigned char>(c)];
+        g.ext[g.n] = make_fastdiv(uint32_t(e));
+        g.s0[g.n] = uint32_t(stride_of(t0, c, ext) * elem);
+        g.s1[g.n] = uint32_t(stride_of(t1, c, ext) * elem);
+        total *= e;
+        ++g.n;
+    }
+    g.total = int32_t(total);
+}
+
+}  // namespace
+
+bool plan_direct(const std::string& modesP, const std::string& modesQ, const std::string& modesC,
+                 const int64_t* ext, int elem, DirectArgs* g) {
+    memset(g, 0, sizeof(*g));
+    // extent-1 modes move nothing
+    std::string P, Q, C;
+    auto keep = [&](const std::string& from, std::string& to) {
+        int64_t v = 1;
+        for (char c : from) {
+            const int64_t e = ext[static_cast<unsigned char>(c)];
+            if (e > 1) to += c;
+            v *= e;
+            if (v * elem >= (int64_t(1) << 32) || v >= kLimit) return false;
+        }
+        return true;
+    };
+    if (!keep(modesP, P) || !keep(modesQ, Q) || !keep(modesC, C)) return false;
+    if (C.empty() || !has(P, C[0]) || has(Q, C[0])) return false;
+    std::string X, Y, K, L;
+    for (char c : C) (has(P, c) ? (has(Q, c) ? L : X) : Y) += c;
+    // the contracted modes in the order of the operand that starts with one
+    const std::string& kFrom = !P.empty() && !has(C, P[0]) ? P : !Q.empty() && !has(C, Q[0]) ? Q : P;
+    for (char c : kFrom)
+        if (!has(C, c)) K += c;
+    // Y in Q's order when Q starts with one of its modes (runs of Q), else C's
+    if (!Q.empty() && has(Y, Q[0])) {
+        Y.clear();
+        for (char c : Q)
+            if (has(C, c) && !has(P, c)) Y += c;
+    }
+    // x2: the X modes P starts with, until they make a run of 8 elements,
+    // unless P starts with C's stride-1 mode (or with a contracted one)
+    std::string x2;
+    int64_t e2 = 1;
+    size_t lead = 0;
+    while (lead < P.size() && has(X, P[lead]) && P[lead] != C[0] && e2 < 8) {
+        e2 *= ext[static_cast<unsigned char>(P[lead])];
+        x2 += P[lead++];
+    }
+    std::string x1;
+    for (char c : X)
+        if (!has(x2, c)) x1 += c;
+    set_group(g->x1, x1, P, C, ext, elem);
+    set_group(g->x2, x2, P, C, ext, elem);
+    set_group(g->y, Y, Q, C, ext, elem);
+    set_group(g->k, K, P, Q, ext, elem);
+    const int logM = ceil_log2(kBM), logN = ceil_log2(kBN), logK = ceil_log2(direct_slice(elem));
+    // Up to 8 positions of x2 (MI355X, fp64 abcde = efbad.cf, runs of 8, 4 and 2
+    // elements in P against runs of 16, 32 and 64 in C: 99, 113 and 132 us).
+    g->t2log = ceil_log2(e2 < 8 ? e2 : 8);
+    g->t1log = logM - g->t2log;
+    if (!x2.empty()) {
+        g->sh2 = 0;
+        if (lead < P.size() && !has(C, P[lead])) {  // then a contracted mode
+            g->shk = g->t2log;
+            g->sh1 = g->t2log + logK;
+        } else {
+            g->sh1 = g->t2log;
+            g->shk = logM;
+        }
+    } else if (!P.empty() && !has(C, P[0])) {  // P starts with a contracted mode
+        g->shk = 0;
+        g->sh1 = logK;
+        g->sh2 = logK + g->t1log;
+    } else {
+        g->sh1 = 0;
+        g->sh2 = g->t1log;
+        g->shk = logM;
+    }
+    if (!Q.empty() && !has(C, Q[0])) {
+        g->shq = 0;
+        g->shn = logK;
+    } else {
+        g->shn = 0;
+        g->shq = logN;
+    }
+    const int64_t t1 = int64_t(1) << g->t1log, t2 = int64_t(1) << g->t2log;
+    const int64_t ny = (g->y.total + kBN - 1) / kBN, n2 = (g->x2.total + t2 - 1) / t2,
+                  n1 = (g->x1.total + t1 - 1) / t1;
+    g->tilesY = make_fastdiv(uint32_t(ny));
+    g->tiles2 = make_fastdiv(uint32_t(n2));
+    g->tiles1 = make_fastdiv(uint32_t(n1));
+    int64_t tiles = ny * n2 * n1;
+    for (char c : L) {
+        const int64_t e = ext[static_cast<unsigned char>(c)];
+        g->eL[g->nL] = make_fastdiv(uint32_t(e));
+        g->sLP[g->nL] = stride_of(P, c, ext) * elem;
+        g->sLQ[g->nL] = stride_of(Q, c, ext) * elem;
+        g->sLC[g->nL] = stride_of(C, c, ext) * elem;
+        ++g->nL;
+        tiles *= e;
+    }
+    if (tiles >= (int64_t(1) << 32) / kBlock) return false;  // a launch counts threads in 32 bits
+    g->numTiles = uint32_t(tiles);
+    // Non-temporal stores of C where it will not stay in the 256 MiB last-level
+    // cache anyway (MI355X, fp64, 226 MB: 59 -> 53 us; fp32, 107 MB: 25 -> 35
+    // us), sooner where its 16-element runs are written by distant blocks
+    // (fp32, 127 MB 61 -> 50 us, 134 MB 60 -> 50 us).
+    int64_t bytesC = elem;
+    for (char c : C) bytesC *= ext[static_cast<unsigned char>(c)];
+    g->streamC = bytesC >= ((x2.empty() ? 128 : 64) << 20);
+    return true;
+}
+
+namespace {
+
+// Two overlapping costs: the larger, and a part of the smaller.
+double overlap(double a, double b) { return a > b ? a + 0.3 * b : b + 0.3 * a; }
+
+double batches(const DirectArgs& g) {
+    double v = 1;
+    for (int j = 0; j < g.nL; ++j) v *= double(g.eL[j].d);
+    return v;
+}
+
+// Bytes of P, Q and C.
+void tensor_bytes(const DirectArgs& g, int elem, double* in, double* out) {
+    const double m = double(g.x1.total) * double(g.x2.total), n = g.y.total, k = g.k.total;
+    *in = (m * k + n * k) * batches(g) * elem;
+    *out = m * n * batches(g) * elem;
+}
+
+}  // namespace
+
+// The constants of both estimates come from 16 benchmark contractions (fp64
+// and fp32) and 24 random ones on MI355X.
+double direct_us(const DirectArgs& g, int elem) {
+    const bool f64 = elem == 8;
+    double in, out;
+    tensor_bytes(g, elem, &in, &out);
+    // runs of C below 64 bytes write parts of its lines
+    int64_t run = elem;
+    for (int j = 0; j < g.x1.n && g.x1.s1[j] == run; ++j) run *= g.x1.ext[j].d;
+    if (run < 64) out *= run < 16 ? 4 : 64.0 / double(run);
+    const int bk = direct_slice(elem);
+    const double slices = (g.k.total + bk - 1) / bk;
+    const double rows = double(g.tiles1.d) * g.tiles2.d * kBM;
+    const double cols = (g.y.total + 15) / 16 * 16.0;  // products of 16 columns are left out
+    const double flops = 2.0 * rows * cols * slices * bk * batches(g);
+    const double stream = overlap(flops / (f64 ? 35e6 : 64e6), (in + out) / 4.2e6);
+    // a block's slices follow each other; about 1024 blocks run at one time
+    const double rounds = (g.numTiles + 1023) / 1024;
+    const double chain = rounds * slices * (f64 ? 1.2 : 2.0);
+    return 7 + (stream > chain ? stream : chain);
+}
+
+double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved) {
+    double in, out;
+    tensor_bytes(g, elem, &in, &out);
+    const double flops =
+        2.0 * g.x1.total * double(g.x2.total) * g.y.total * double(g.k.total) * batches(g);
+    return 9 + 5.5 * transposes + bytesMoved / 4.5e6 +
+           overlap(flops / (elem == 8 ? 58e6 : 125e6), (in + out) / 4e6);
+}
+
+}  // namespace hptt

@@ -233,6 +233,8 @@ hptt_status_t launch(const hptt_plan_s* p, const void* A, void* B, hipStream_t s
 }  // namespace
 }  // namespace hptt
 
+void hptt::record_hip_error(hipError_t err) { g_last_hip_error = int32_t(err); }
+
 extern "C" {
 
 hptt_status_t hptt_exec(hptt_plan_t plan, const void* A, void* B, hipStream_t stream) {

@@ -23,6 +23,9 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
                          double beta, hptt_dtype_t dtype, const hptt_options_t* options,
                          hptt_plan_s* plan);
 
+// Keep a failed launch's error for hptt_last_hip_error (this thread).
+void record_hip_error(hipError_t err);
+
 // LDS bytes of kernel T: the two offset tables and the padded tile.
 int64_t tile_lds_bytes_host(const TileArgs& t, int elem);
 

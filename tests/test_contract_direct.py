@@ -1,0 +1,82 @@
+"""The direct contraction kernel's planner and index arithmetic on the CPU:
+random contractions of every mix of roles, against the contraction oracle on
+whole numbers (exact in any order), with every offset checked, and the blocks
+of the benchmark contractions at full size."""
+from __future__ import annotations
+
+import ctypes
+
+import numpy as np
+
+from emulator import build as emu_build
+from oracle import contract as oc
+
+
+def _library():
+    lib = ctypes.CDLL(emu_build.build_direct())
+    vp = ctypes.c_void_p
+    lib.direct_emulate.argtypes = [ctypes.c_char_p] * 3 + [vp, ctypes.c_double, ctypes.c_double, vp,
+                                                            vp, vp, vp, ctypes.c_int64, ctypes.c_char_p,
+                                                            ctypes.c_size_t]
+    lib.direct_emulate.restype = ctypes.c_int64
+    return lib
+
+
+def _run(lib, a, b, c, ext, alpha=1.0, beta=0.0, A=None, B=None, C=None, counts=None, stride=1):
+    e = np.zeros(256, dtype=np.int64)
+    for m, n in ext.items():
+        e[ord(m)] = n
+    msg = ctypes.create_string_buffer(256)
+    ptr = [None if x is None else x.ctypes.data for x in (A, B, C, counts)]
+    rc = lib.direct_emulate(a.encode(), b.encode(), c.encode(), e.ctypes.data, alpha, beta, *ptr,
+                            stride, msg, len(msg))
+    return rc, msg.value.decode()
+
+
+def test_random_contractions_match_oracle():
+    lib = _library()
+    rng = np.random.default_rng(1704)
+    ran = refused = 0
+    while ran < 250:
+        modes = "abcdefg"[:int(rng.integers(2, 8))]
+        roles = rng.integers(0, 4, size=len(modes))
+        if rng.random() < 0.7:
+            roles[roles == 3] = 2       # most without batch modes
+        t = [[m for m, r in zip(modes, roles) if r in keep] for keep in ((0, 2, 3), (1, 2, 3),
+                                                                         (0, 1, 3))]
+        if not t[0] or not t[1]:
+            continue
+        for x in t:
+            rng.shuffle(x)
+        a, b, c = ("".join(x) for x in t)
+        ext = {m: int(rng.choice([1, 2, 3, 5, 8, 9, 17, 33])) for m in modes}
+        vol = lambda s: int(np.prod([ext[m] for m in s], dtype=np.int64))
+        if vol(a) > 20000 or vol(b) > 20000 or vol(c) > 20000 or vol(modes) > 400000:
+            continue
+        sa, sb = [ext[m] for m in a], [ext[m] for m in b]
+        A, B, C = (rng.integers(-4, 5, size=vol(s)).astype(np.float64) for s in (a, b, c))
+        alpha, beta = [(1.0, 0.0), (0.5, -2.0)][ran % 2]
+        counts = np.zeros(C.size, dtype=np.uint8)
+        got = C.copy()
+        rc, msg = _run(lib, a, b, c, ext, alpha, beta, A, B, got, counts)
+        if rc == -1:   # C starts with a batch mode, or is a scalar
+            first = next((m for m in c if ext[m] > 1), None)
+            assert first is None or (first in a and first in b), (a, b, c, ext)
+            refused += 1
+            continue
+        assert rc == 0, (a, b, c, ext, msg)
+        assert (counts == 1).all(), (a, b, c, ext)
+        want = oc.contract(A, a, sa, B, b, sb, c, alpha, beta, C)
+        assert np.array_equal(got, want), (a, b, c, ext)
+        ran += 1
+    assert refused < ran
+
+
+def test_workload_blocks():
+    """Offsets of a sample of the blocks of every benchmark contraction."""
+    from paper_1704_04374_amd.workloads import CONTRACTIONS
+    lib = _library()
+    for w in CONTRACTIONS:
+        rc, msg = _run(lib, w.modes_a, w.modes_b, w.modes_c, w.ext(), stride=max(
+            1, w.numel(w.modes_c) // (128 * 64 * 20)))
+        assert rc == 0, (w.name, msg)
