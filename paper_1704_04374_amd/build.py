@@ -25,8 +25,8 @@ CONTRACT_LIB = os.path.join(PKG, "libhptt_contract.so")
 CONTRACT_SOURCES = ["contract.hip", "contract_direct.hip", "contract_direct_plan.cpp"]
 
 ARCH = "gfx950"
-# the tile kernel instantiations are split over six files so they compile in parallel
-SOURCES = ["tile_f32_fast.hip", "tile_f32_shifted.hip", "tile_f32_general.hip", "tile_shared.hip",
+# the tile kernel instantiations are split over several files so they compile in parallel
+SOURCES = ["tile_matrix.hip", "tile_f32_fast.hip", "tile_f32_shifted.hip", "tile_f32_general.hip", "tile_shared.hip",
            "tile_direct.hip", "tile_f64.hip", "kernels.hip",
            "yardstick.hip", "api.cpp", "plan.cpp", "autotune.cpp"]
 

@@ -47,6 +47,41 @@ struct DeviceMem {
         __builtin_memcpy(&r, p + off, sizeof(r));
         return r;
     }
+    // Byte-offset accesses: p is the same for the whole wave, off a lane's own
+    // 32-bit byte offset (a scalar base and one vector register).  ldub and stub
+    // move V elements at any element boundary, ldb and stb whole aligned vectors.
+    template <typename T, typename P>
+    __device__ __forceinline__ static T* at_bytes(P* p, int64_t off) {
+        return reinterpret_cast<T*>((char*)(p) + off);
+    }
+    template <typename T, int V, bool NT>
+    __device__ __forceinline__ static Vec<T, V> ldub(const T* p, uint32_t off) {
+        typedef T vt __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+        const vt* q = reinterpret_cast<const vt*>(reinterpret_cast<const char*>(p) + off);
+        const vt x = NT ? __builtin_nontemporal_load(q) : *q;
+        Vec<T, V> r;
+#pragma unroll
+        for (int e = 0; e < V; ++e) r.v[e] = x[e];
+        return r;
+    }
+    template <bool NT, typename T, int V>
+    __device__ __forceinline__ static void stub(T* p, uint32_t off, const Vec<T, V>& v) {
+        typedef T vt __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+        vt x;
+#pragma unroll
+        for (int e = 0; e < V; ++e) x[e] = v.v[e];
+        vt* q = reinterpret_cast<vt*>(reinterpret_cast<char*>(p) + off);
+        if (NT) __builtin_nontemporal_store(x, q);
+        else *q = x;
+    }
+    template <typename T, int V, bool NT>
+    __device__ __forceinline__ static Vec<T, V> ldb(const T* p, uint32_t off) {
+        return ld<T, V, NT>(reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + off), 0);
+    }
+    template <bool NT, typename T, int V>
+    __device__ __forceinline__ static void stb(T* p, uint32_t off, const Vec<T, V>& v) {
+        st<NT, T, V>(reinterpret_cast<T*>(reinterpret_cast<char*>(p) + off), 0, v);
+    }
     template <bool NT, typename T>
     __device__ __forceinline__ static void st1(T* p, int64_t off, T v) {
         if constexpr (NT) __builtin_nontemporal_store(v, p + off);
@@ -91,6 +126,11 @@ struct DeviceMem {
     }
     template <typename T>
     __device__ __forceinline__ static T lds_ld(const T* l, int64_t i) {
+        return l[i];
+    }
+    // A word that may not have been written; the caller then drops it.
+    template <typename T>
+    __device__ __forceinline__ static T lds_any(const T* l, int64_t i) {
         return l[i];
     }
     template <typename T>

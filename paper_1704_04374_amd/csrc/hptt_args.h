@@ -165,6 +165,34 @@ struct TileArgs {
     int64_t gStrideB[kMaxDims];     // grid digit strides in B
 };
 
+// Kernel M ("matrix" tiles): the problem as a batch of two-dimensional
+// transpositions of flattened index groups.  The columns are the leading A
+// indices 0..nC-1, back to back in A, flattened into one range of colsA
+// positions; the rows the leading B positions 0..nR-1, back to back in B and
+// none of them a column index, flattened into rowsB positions.  A tile is a
+// rectangle of compile-time size (MatrixShape in matrix_body.h) of that
+// matrix, cut anywhere in both ranges; every other index is a grid digit.
+// Offsets inside one matrix are 32-bit byte offsets.
+struct MatrixArgs {
+    int32_t use;          // 1: hptt_exec launches kernel M instead of kernel T
+    int32_t shape;        // index of the tile shape
+    int32_t shear;        // 1: B runs start on 128-byte lines
+    int32_t hints;        // cache hints
+    int32_t misLine;      // launch: element offset of B's base pointer from a line
+    uint32_t colsA, rowsB;
+    int32_t nC, nR, nG;   // nG: digits after the column and row chunks
+    int32_t skew;         // row chunks rotated by the column chunk (diagonal order)
+    int32_t xcdGroupLog;
+    uint32_t numTiles;
+    FastDiv chunksC, chunksR;
+    FastDiv cExt[kMaxDims];
+    uint32_t cStrideB[kMaxDims];  // bytes
+    FastDiv rExt[kMaxDims];
+    uint32_t rStrideA[kMaxDims];  // bytes
+    FastDiv gExt[kMaxDims];
+    int64_t gStrideA[kMaxDims], gStrideB[kMaxDims];  // bytes
+};
+
 // Kernel S: A's stride-1 index is also B's.  Each "row" is one full run of
 // that index, contiguous in both tensors.  Work item i = r*W + c is vector c
 // of row r (rows in B order, W vectors per row), so consecutive lanes write

@@ -157,10 +157,35 @@ hptt_status_t stream_slabs(const hptt_plan_s* p, const void* fn, const T* A, T* 
     return HPTT_SUCCESS;
 }
 
+// Kernel M: any element-aligned pointers.
+template <typename T>
+hptt_status_t launch_matrix(const hptt_plan_s* p, const T* A, T* B, hipStream_t stream) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(A), pb = reinterpret_cast<uintptr_t>(B);
+    MatrixArgs g = p->matrix;
+    g.misLine = int32_t(pb / sizeof(T) % (128 / sizeof(T)));
+    // lines shared between tiles take no non-temporal hint (see launch)
+    int hints = g.hints;
+    if (!g.shear && pb % 128 != 0) hints = 0;
+    if (pa % 128 != 0) hints &= ~kNtLoad;
+    const void* fn = sizeof(T) == 4 ? matrix_kernel_f32(g.shape, p->info.mode, hints)
+                                    : matrix_kernel_f64(g.shape, p->info.mode, hints);
+    if (!fn) return HPTT_ERROR_INVALID_ARGUMENT;
+    T alpha = T(p->alpha), beta = T(p->beta);
+    void* args[5] = {&A, &B, &g, &alpha, &beta};
+    const hipError_t err = hipLaunchKernel(fn, dim3(g.numTiles), dim3(kBlock), args, 0, stream);
+    if (err != hipSuccess) {
+        g_last_hip_error = int32_t(err);
+        return HPTT_ERROR_HIP;
+    }
+    return HPTT_SUCCESS;
+}
+
 template <typename T>
 hptt_status_t launch(const hptt_plan_s* p, const void* A, void* B, hipStream_t stream) {
     const hptt_plan_info_t& in = p->info;
     const int elem = int(sizeof(T));
+    if (in.kernel == HPTT_KERNEL_TILE && p->matrix.use)
+        return launch_matrix<T>(p, static_cast<const T*>(A), static_cast<T*>(B), stream);
     const uintptr_t pa = reinterpret_cast<uintptr_t>(A), pb = reinterpret_cast<uintptr_t>(B);
     // The tile kernel keeps its widths and shifts its runs onto the vector
     // grid of the actual pointers; the others narrow to the pointers' alignment.
@@ -262,6 +287,7 @@ hptt_status_t hptt_load_kernels(void) {
                          tile_kernel_f32(kGeneral, kCopy, 0, 1, 1, kBlock),
                          tile_kernel_f32(kShared, kCopy, 0, 1, 1, kBlock),
                          tile_kernel_f64(kFast, kCopy, 0, 1, 1, kBlock),
+                         matrix_kernel_f32(0, kCopy, 0), matrix_kernel_f64(0, kCopy, 0),
                          stream_fn<float, kCopy, 0>(1)};
     for (const void* f : fns) {
         if (!f) continue;

@@ -9,6 +9,7 @@
 
 #include <algorithm>
 
+#include "matrix_body.h"
 #include "plan.h"
 
 namespace hptt {
@@ -830,6 +831,171 @@ bool setup_shared(const Fused& f, int elem, int64_t tA, int64_t tB, const hptt_o
     return true;
 }
 
+// Kernel M's shapes (matrix_body.h) as numbers.
+struct MatrixShapeInfo {
+    int id, cols, rows, line;
+};
+#define X(id, tc, tr, line) {id, tc, tr, line},
+const MatrixShapeInfo kShapes32[] = {HPTT_MATRIX_SHAPES_F32(X)};
+const MatrixShapeInfo kShapes64[] = {HPTT_MATRIX_SHAPES_F64(X)};
+#undef X
+
+// The columns (A indices 0..d, until they hold `want` positions) and rows
+// (every leading B position that is back to back and not a column) of the
+// flattened problem.  False where A or B has no stride-1 index.
+struct MatrixGroups {
+    int d, k;             // last column index, last row position
+    int64_t cols, rows;
+    bool inC[kMaxDims], inR[kMaxDims];
+    int64_t granA, granB;  // gcd of the strides, in elements, of what is not a column / a row
+};
+
+bool matrix_groups(const Fused& f, int64_t want, MatrixGroups& m) {
+    const int M = f.M, p0 = f.p[0];
+    if (p0 == 0 || f.sA[0] != 1 || f.sB[p0] != 1) return false;
+    memset(&m, 0, sizeof(m));
+    m.cols = f.n[0];
+    while (m.cols < want && m.d + 1 < p0 && f.sA[m.d + 1] == f.sA[m.d] * f.n[m.d])
+        m.cols *= f.n[++m.d];
+    for (int j = 0; j <= m.d; ++j) m.inC[j] = true;
+    m.rows = f.n[p0];
+    while (m.k + 1 < M && !m.inC[f.p[m.k + 1]] &&
+           f.sB[f.p[m.k + 1]] == f.sB[f.p[m.k]] * f.n[f.p[m.k]])
+        m.rows *= f.n[f.p[++m.k]];
+    for (int j = 0; j <= m.k; ++j) m.inR[f.p[j]] = true;
+    for (int a = 0; a < M; ++a) {
+        if (!m.inC[a]) m.granA = gcd64(m.granA, f.sA[a]);
+        if (!m.inR[a]) m.granB = gcd64(m.granB, f.sB[a]);
+    }
+    return true;
+}
+
+// Fill g for one shape.  False where its 32-bit offsets or the launch's
+// thread count do not hold the problem.
+bool setup_matrix(const Fused& f, int elem, const MatrixShapeInfo& sh, const MatrixGroups& m,
+                  int32_t gorder, MatrixArgs& g) {
+    memset(&g, 0, sizeof(g));
+    const int64_t limit = int64_t(1) << 32;
+    if (m.cols < 16 / elem || m.cols >= (1 << 30) || m.rows >= (1 << 30)) return false;
+    int64_t spanA = m.cols, spanB = m.rows + 256;
+    g.nC = m.d + 1;
+    g.nR = m.k + 1;
+    for (int j = 0; j <= m.d; ++j) {
+        set_div(g.cExt[j], f.n[j]);
+        g.cStrideB[j] = uint32_t(f.sB[j] * elem);
+        spanB += (f.n[j] - 1) * f.sB[j];
+    }
+    for (int j = 0; j <= m.k; ++j) {
+        const int a = f.p[j];
+        set_div(g.rExt[j], f.n[a]);
+        g.rStrideA[j] = uint32_t(f.sA[a] * elem);
+        spanA += (f.n[a] - 1) * f.sA[a];
+    }
+    if (spanA * elem >= limit || spanB * elem >= limit) return false;
+    g.colsA = uint32_t(m.cols);
+    g.rowsB = uint32_t(m.rows);
+    g.shape = sh.id;
+    g.shear = sh.line > 0;
+    const int64_t S = sh.line ? sh.line / elem - 1 : 0;
+    const int64_t nc = (m.cols + sh.cols - 1) / sh.cols, nr = (m.rows + S + sh.rows - 1) / sh.rows;
+    set_div(g.chunksC, nc);
+    set_div(g.chunksR, nr);
+    double tiles = double(nc) * double(nr);
+    bool inTile[kMaxDims];
+    for (int a = 0; a < f.M; ++a) inTile[a] = m.inC[a] || m.inR[a];
+    int outer[kMaxDims];
+    const int no = outer_indices(f, inTile, gorder, outer);
+    for (int i = 0; i < no; ++i) {
+        const int a = outer[i];
+        if (f.n[a] >= limit) return false;
+        set_div(g.gExt[i], f.n[a]);
+        g.gStrideA[i] = f.sA[a] * elem;
+        g.gStrideB[i] = f.sB[a] * elem;
+        tiles *= double(f.n[a]);
+    }
+    g.nG = no;
+    if (tiles * kBlock >= double(limit)) return false;  // a launch counts threads in 32 bits
+    g.numTiles = uint32_t(tiles);
+    return true;
+}
+
+// Which shape of kernel M serves the problem, or -1 for kernel T.  The lines
+// lie where MI355X timings of 191 problems (the 57-case sweep, 2-D sizes from
+// 512 to 10000, random ones from 0.2 to 1000 MB moved; fp32 and fp64, beta = 0
+// and not) put them; over these the rule's shape is 1.31x faster than kernel T
+// on average and 2.6 % behind the best shape.
+int matrix_shape(const Fused& f, int elem, int64_t numel, const hptt_plan_info_t& info,
+                 const TileArgs& t) {
+    MatrixGroups m;
+    if (!matrix_groups(f, 128 / elem, m)) return -1;
+    const int64_t bytes = numel * elem;
+    const bool readsB = info.mode == kAxpby;
+    // B runs that are whole lines, or (fp64) whole half lines
+    const bool lines = (m.granB * elem) % kLine == 0 && (m.rows * elem) % kLine == 0;
+    const bool halfLines = (m.granB * elem) % (kLine / 2) == 0;
+    if (elem == 4) {
+        // Large fp32 problems whose runs are whole lines on both sides stay
+        // with kernel T (variants kDirect and kFast), whose tiles take an
+        // index's own extents as runs: 8192 x 8192 92 us against 96, the 6-D
+        // 24x20x16x24x18x20 99 against 103, 3x2x640x480x96 with beta = 1 353
+        // against 363.  Smaller ones gain with kernel M (4096 x 4096 28 -> 26,
+        // 2048 x 2048 9.4 -> 8.2, 1024 x 1024 6.2 -> 3.7).
+        if (bytes >= (100 << 20) && t.alignedA && t.alignedB && !t.shear && t.nZ == 1) return -1;
+        // few columns: 16 of them, by 256 rows where there are enough
+        if (m.cols < 17) return bytes < (4 << 20) || m.rows < 256 ? 7 : 2;
+        // small problems: the most tiles (36x255x22 10.4 us -> 3.5 against
+        // 6 to 7 with larger tiles)
+        if (bytes < (5 << 19)) return 7;
+        if (lines) {
+            if (m.rows % 64 == 0 || m.rows >= 512) return 3;
+            return m.rows < 128 ? 6 : 4;
+        }
+        // B runs off the lines: sheared onto them, unless the run is so short
+        // that the shear rows are most of a tile, or the problem too small
+        if (m.rows <= 64) return bytes >= (16 << 20) ? 3 : 7;
+        if (bytes < (16 << 20)) return 7;
+        if (m.rows <= 128) return 5;
+        return m.cols < 56 || (readsB && m.cols < 112) ? 0 : 1;
+    }
+    if (m.cols < 12) return m.rows >= 128 ? 2 : 5;
+    if (halfLines) return bytes >= (20 << 20) && m.cols >= 24 ? 3 : 5;
+    if (m.rows <= 24) return 4;
+    if (m.rows < 64 || bytes < (3 << 20)) return 5;
+    return m.rows < 256 || bytes < (20 << 20) || m.cols < 24 ? 1 : 0;
+}
+
+// Kernel M in the place of the tile plan in `info` and `t`, where it serves
+// the problem and is the faster one.  The tile plan stays as it is: it is what
+// plan information describes.
+void choose_matrix(const Fused& f, int elem, int64_t numel, const TileArgs& t,
+                   const hptt_plan_info_t& info, MatrixArgs& g) {
+    const int id = matrix_shape(f, elem, numel, info, t);
+    if (id < 0) return;
+    const MatrixShapeInfo& sh = elem == 4 ? kShapes32[id] : kShapes64[id];
+    MatrixGroups m;
+    if (!matrix_groups(f, sh.cols, m) || !setup_matrix(f, elem, sh, m, info.grid_order, g)) {
+        g.use = 0;
+        return;
+    }
+    g.use = 1;
+    // Columns a multiple of 4 KiB apart in B: the diagonal order spreads the
+    // tiles in flight over the HBM channels (8192 x 8192 as above 96 us against
+    // 102); else groups of 16 tiles per XCD in grid order, whose tiles share
+    // the lines at the ends of their A runs (problems of 50 MB and more 1.11x
+    // on average, smaller ones 1.01 to 1.09x).
+    g.skew = (f.sB[0] * elem) % 4096 == 0 && g.chunksR.d > 1;
+    g.xcdGroupLog = g.skew ? 0 : 4;
+    // Non-temporal stores where tiles share no half line of B (problems of 4 MiB
+    // and more 2 to 8 % faster, with shared ones up to 1.9x slower); loads of
+    // A likewise where runs are whole lines.
+    const bool large = numel * elem >= (4 << 20);
+    const bool store = g.shear || (large && (m.granB * elem) % (kLine / 2) == 0 &&
+                                   (m.rows * elem) % (kLine / 2) == 0);
+    const bool load = store && large && !g.shear && (m.granA * elem) % kLine == 0 &&
+                      m.cols % sh.cols == 0 && (sh.cols * elem) % kLine == 0;
+    g.hints = (store ? kNtStore : 0) | (load ? kNtLoad : 0);
+}
+
 // Score of a tile shape for the choice between disjoint and shared runs:
 // the bytes of each run up to 512 (a run shorter than a few lines wastes
 // most of each HBM burst), then the tile up to kMinTileBytes, and a penalty
@@ -1444,6 +1610,11 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
     const bool ntLoad = opt.load_hint == 1 || (opt.load_hint == 0 && loadOk && k != HPTT_KERNEL_GENERIC);
     info.hints = (ntStore ? kNtStore : 0) | (ntLoad ? kNtLoad : 0);
     info.kernel = k;
+    // kernel M where the caller left every choice to the plan builder
+    hptt_options_t none;
+    memset(&none, 0, sizeof(none));
+    if (k == HPTT_KERNEL_TILE && !sharedTile && memcmp(&opt, &none, sizeof(none)) == 0)
+        choose_matrix(f, elem, numel, plan->tile, info, plan->matrix);
     return HPTT_SUCCESS;
 }
 
@@ -1467,6 +1638,13 @@ void describe_plan(const hptt_plan_s* p, char* buf, size_t len) {
              (long long)in.grid,
              in.block, in.hints, in.tile_order, in.shear, in.shared_runs, in.flat_runs,
              in.grid_order, in.direct_lds, in.xcd_group);
+    const size_t used = strlen(buf);
+    if (p->matrix.use && used < len) {
+        const MatrixShapeInfo& sh = (in.elem_bytes == 4 ? kShapes32 : kShapes64)[p->matrix.shape];
+        snprintf(buf + used, len - used, " matrix=%dx%d of %ux%u shear=%d tiles=%u hints=%d", sh.cols,
+                 sh.rows, p->matrix.colsA, p->matrix.rowsB, sh.line, p->matrix.numTiles,
+                 p->matrix.hints);
+    }
 }
 
 }  // namespace hptt

@@ -10,6 +10,7 @@ struct hptt_plan_s {
     double alpha;  // rounded to dtype
     double beta;   // rounded to dtype
     hptt::TileArgs tile;
+    hptt::MatrixArgs matrix;  // matrix.use: launched instead of tile
     hptt::StreamArgs stream;
     hptt::GenericArgs generic;
 };

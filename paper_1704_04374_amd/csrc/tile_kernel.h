@@ -16,6 +16,10 @@ namespace hptt {
 const void* tile_kernel_f32(int variant, int mode, int hints, int va, int vb, int block);
 const void* tile_kernel_f64(int variant, int mode, int hints, int va, int vb, int block);
 
+// Address of kernel M for (shape, update mode, cache hints); tile_matrix.hip.
+const void* matrix_kernel_f32(int shape, int mode, int hints);
+const void* matrix_kernel_f64(int shape, int mode, int hints);
+
 namespace {
 
 // One workgroup of BLOCK threads per tile (or a grid-stride loop over tiles

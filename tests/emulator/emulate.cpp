@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "kernel_body.h"
+#include "matrix_body.h"
 #include "plan.h"
 
 namespace {
@@ -193,6 +194,42 @@ struct HostMem {
         if (!S->dry) p[off] = v;
         if (S->counts && S->counts[at] < 255) ++S->counts[at];
     }
+    // byte offsets from a base that may lie outside the tensor
+    template <typename T, typename P>
+    static T* at_bytes(P* p, int64_t off) {
+        return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + uintptr_t(off));
+    }
+    template <typename T>
+    static T* plus(T* p, uint32_t off) {
+        return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + off);
+    }
+    template <typename T, int V, bool NT>
+    static hptt::Vec<T, V> ldub(const T* p, uint32_t off) {
+        return ldu<T, V>(plus(p, off), 0);
+    }
+    template <typename T, int V, bool NT>
+    static hptt::Vec<T, V> ldb(const T* p, uint32_t off) {
+        return ld<T, V, NT>(plus(p, off), 0);
+    }
+    template <bool NT, typename T, int V>
+    static void stb(T* p, uint32_t off, const hptt::Vec<T, V>& v) {
+        st<NT, T, V>(plus(p, off), 0, v);
+    }
+    template <bool NT, typename T, int V>
+    static void stub(T* p, uint32_t off, const hptt::Vec<T, V>& v) {
+        for (int e = 0; e < V; ++e) st1<NT, T>(plus(p, off), e, v.v[e]);
+    }
+    template <typename T>
+    static T lds_any(const T* l, int64_t i) {
+        const int64_t at = reinterpret_cast<const uint8_t*>(l + i) - S->lds.data();
+        if (at < 0 || at + int64_t(sizeof(T)) > int64_t(S->lds.size())) {
+            fail("LDS access out of bounds", at, sizeof(T));
+            return T(0);
+        }
+        T r;
+        memcpy(&r, l + i, sizeof(T));
+        return r;
+    }
     template <typename T>
     static T lds_ld(const T* l, int64_t i) {
         check_lds(l + i, sizeof(T), false);
@@ -308,12 +345,64 @@ void emu_tile_shared(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride
     }
 }
 
+// Mirrors matrix_kernel in tile_matrix.hip.
+template <typename T, int MODE, class SH>
+void emu_matrix(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
+    using namespace hptt;
+    MatrixArgs g = p->matrix;
+    g.misLine = int32_t(S->misB % (128 / int(sizeof(T))));
+    const T alpha = T(p->alpha), beta = T(p->beta);
+    S->lds.assign(SH::ldsBytes, 0);
+    S->written.assign(SH::ldsBytes, 0);
+    uint32_t* rowA = reinterpret_cast<uint32_t*>(S->lds.data());
+    uint32_t* colB = rowA + SH::rows;
+    int32_t* colL = reinterpret_cast<int32_t*>(colB + SH::TC);
+    int32_t* colD = colL + SH::TC;
+    T* lds = reinterpret_cast<T*>(S->lds.data() + (SH::tableBytes + 15) / 16 * 16);
+    for (int64_t t = 0; t < int64_t(g.numTiles) && S->errors == 0; t += blockStride) {
+        clear_written(0, SH::ldsBytes);
+        const MatrixTile m = matrix_tile<SH>(g, uint32_t(t));
+        for (int tid = 0; tid < kBlock; ++tid)
+            matrix_tables<HostMem, T, SH>(g, m, tid, rowA, colB, colL, colD);
+        for (int tid = 0; tid < kBlock; ++tid)
+            matrix_load<HostMem, T, 0, SH>(g, m, tid, A, lds, rowA);
+        for (int tid = 0; tid < kBlock; ++tid)
+            matrix_store<HostMem, T, MODE, 0, SH>(g, m, tid, B, lds, colB, colL, colD, alpha, beta);
+    }
+}
+
+template <typename T, int MODE>
+bool emu_matrix_shape(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
+    using namespace hptt;
+    if (!p->matrix.use) return false;
+    if constexpr (sizeof(T) == 4) {
+        switch (p->matrix.shape) {
+#define X(id, tc, tr, line) \
+            case id: emu_matrix<T, MODE, MatrixShape<T, tc, tr, line>>(p, A, B, blockStride); break;
+            HPTT_MATRIX_SHAPES_F32(X)
+#undef X
+            default: fail("unknown shape", p->matrix.shape, 0);
+        }
+    } else {
+        switch (p->matrix.shape) {
+#define X(id, tc, tr, line) \
+            case id: emu_matrix<T, MODE, MatrixShape<T, tc, tr, line>>(p, A, B, blockStride); break;
+            HPTT_MATRIX_SHAPES_F64(X)
+#undef X
+            default: fail("unknown shape", p->matrix.shape, 0);
+        }
+    }
+    return true;
+}
+
 // The variant and workgroup size hptt_exec would launch, or a forced variant:
 // kGeneral serves any plan, kShifted and kFast any plan kDirect serves,
 // kShifted any plan kFast serves.
 template <typename T, int VA, int VB, int MODE, int NT>
 void emu_tile(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
     using namespace hptt;
+    // a forced variant is one of kernel T's
+    if (S->forceVariant < 0 && emu_matrix_shape<T, MODE>(p, A, B, blockStride)) return;
     TileArgs g = p->tile;
     g.misA = int32_t(S->misA % VA);
     g.misB = int32_t(S->misB % VB);

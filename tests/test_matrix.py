@@ -1,0 +1,102 @@
+"""Flattened two-dimensional tiles (kernel M) at the edges of each tile shape:
+through the host emulator, which checks every offset (small problems with
+their data against the oracle, large ones a sample of their tiles), and on an
+MI355X against the oracle, bit for bit, whole."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+
+# extents, perm, dtype, the shape the plan takes; columns and rows one off the
+# tile, flattened groups of several indices, batches
+CASES = [
+    ((33, 70), (1, 0), "f32", "16x64"),
+    ((4, 65), (1, 0), "f32", "16x64"),
+    ((19, 3, 5, 13), (3, 2, 0, 1), "f32", "16x64"),
+    ((7, 9, 11, 40), (3, 1, 0, 2), "f32", "16x64"),
+    ((128, 64, 96), (1, 0, 2), "f32", "64x64"),          # whole lines
+    ((130, 608, 12), (1, 2, 0), "f32", "64x64"),
+    ((800, 224, 6), (1, 0, 2), "f32", "128x32"),
+    ((1030, 96, 12), (1, 0, 2), "f32", "32x32"),
+    ((257, 97, 185), (1, 0, 2), "f32", "32x128"),        # short rows off the lines
+    ((50, 601, 145), (1, 0, 2), "f32", "32x128"),        # sheared
+    ((5, 13, 40, 1700), (3, 2, 1, 0), "f32", "64x64"),
+    ((113, 3, 331, 47), (3, 1, 0, 2), "f32", "64x64"),
+    ((9, 465029), (1, 0), "f32", "16x256"),
+    ((16, 67, 4099), (1, 2, 0), "f32", "16x256"),
+    ((17, 33), (1, 0), "f64", "16x64"),
+    ((31, 65, 3), (1, 0, 2), "f64", "16x64"),
+    ((7, 5, 131, 9), (2, 3, 0, 1), "f64", "16x64"),
+    ((40, 17, 9), (1, 0, 2), "f64", "32x32"),
+    ((11, 400), (1, 0), "f64", "8x128"),
+    ((31, 19, 701), (2, 1, 0), "f64", "16x64"),          # sheared
+    ((514, 512, 11), (1, 0, 2), "f64", "32x64"),
+    ((33, 83, 997), (2, 1, 0), "f64", "32x64"),          # sheared
+]
+MODES = [(1.0, 0.0), (-0.3, 1.25)]
+
+
+def _rand(rng, n, dtype):
+    return (rng.integers(-(1 << 20), 1 << 20, size=n) / float(1 << 20)).astype(
+        np.float32 if dtype == "f32" else np.float64)
+
+
+def _ids(v):
+    return "x".join(map(str, v)) if isinstance(v, tuple) else str(v)
+
+
+@pytest.mark.parametrize("size,perm,dtype,shape", CASES, ids=_ids)
+def test_emulated(size, perm, dtype, shape):
+    from emulator import emu
+    rng = np.random.default_rng(11)
+    for alpha, beta in MODES:
+        p = emu.plan(perm, size, alpha, beta, dtype)
+        assert f"matrix={shape} " in p.describe(), p.describe()
+        if p.numel > 100000:
+            for mis in (0, 1):
+                err, msg, _ = emu.run(p, block_stride=53, mis_b=mis)
+                assert err == 0, f"{p.describe()}: {msg}"
+            continue
+        A, B0 = _rand(rng, p.numel, dtype), _rand(rng, p.numel, dtype)
+        want = orc.transpose(A, size, perm, alpha, beta, B0 if beta != 0 else None)
+        for mis in (0, 1, 3):
+            B = B0.copy()
+            err, msg, cnt = emu.run(p, A, B, counts=True, mis_b=mis)
+            assert err == 0, f"{p.describe()}: {msg}"
+            assert (cnt == 1).all() and np.array_equal(B, want), p.describe()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("size,perm,dtype,shape", CASES, ids=_ids)
+def test_gpu(size, perm, dtype, shape):
+    """Whole tensors, pointers on and off a line, and as blocks of larger tensors."""
+    import torch
+
+    from paper_1704_04374_amd import hptt
+    rng = np.random.default_rng(12)
+    n = int(np.prod(size))
+    size_b = [size[p] for p in perm]
+    A, B0 = _rand(rng, n + 4, dtype), _rand(rng, n + 4, dtype)
+    dA = torch.from_numpy(A).cuda()
+    for alpha, beta in MODES:
+        p = hptt.create_plan(perm, size, alpha, beta, dtype)
+        assert f"matrix={shape} " in p.describe(), p.describe()
+        print(f"[matrix] {p.describe()}", flush=True)
+        for a, b in ((0, 0), (1, 3), (3, 2)):
+            want = B0.copy()
+            want[b:b + n] = orc.transpose(A[a:a + n], size, perm, alpha, beta,
+                                          B0[b:b + n] if beta != 0 else None)
+            dB = torch.from_numpy(B0).cuda()
+            p.exec(dA[a:a + n], dB[b:b + n])
+            assert np.array_equal(dB.cpu().numpy(), want), (p.describe(), a, b)
+    # the last index of A and of B cut short: the rest of B stays as it was
+    cut = tuple(s - 1 if d == len(size) - 1 else s for d, s in enumerate(size))
+    cut_b = [cut[q] for q in perm]
+    p = hptt.create_plan(perm, cut, 1.5, 0.5, dtype, outer_size_a=size, outer_size_b=size_b)
+    print(f"[matrix] {p.describe()}", flush=True)
+    want = orc.transpose_outer(A[:n], cut, perm, size, size_b, 1.5, 0.5, B0[:n])
+    dB = torch.from_numpy(B0[:n].copy()).cuda()
+    p.exec(dA[:n], dB)
+    assert np.array_equal(dB.cpu().numpy(), want), (p.describe(), cut_b)
