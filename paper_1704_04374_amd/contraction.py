@@ -5,6 +5,7 @@ workspace is device memory from torch's allocator."""
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 from . import hptt
@@ -94,6 +95,12 @@ class Contraction:
         hptt._check(st, "hptt_contraction_create")
         self._handle = handle
         self._workspace = None
+        # what every exec needs of the plan, which never changes
+        info = ContractionInfo()
+        hptt._check(self._lib.hptt_contraction_info(handle, ctypes.byref(info)),
+                    "hptt_contraction_info")
+        self._workspace_bytes = info.workspace_bytes
+        self._numel = tuple(math.prod(n) for n in (self.size_a, self.size_b, self.size_c))
 
     @property
     def info(self) -> dict:
@@ -111,16 +118,13 @@ class Contraction:
     def workspace(self):
         """The device workspace this plan executes with (allocated once)."""
         import torch
-        need = self.info["workspace_bytes"]
+        need = self._workspace_bytes
         if need and (self._workspace is None or self._workspace.numel() < need):
             self._workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
         return self._workspace
 
     def _check_tensors(self, A, B, C):
-        for t, name, n in ((A, "A", self.size_a), (B, "B", self.size_b), (C, "C", self.size_c)):
-            numel = 1
-            for s in n:
-                numel *= s
+        for t, name, numel in zip((A, B, C), "ABC", self._numel):
             if not t.is_cuda or not t.is_contiguous() or t.numel() != numel:
                 raise ValueError(f"{name} must be a contiguous device tensor of {numel} elements")
             if hptt._dtype_id(t.dtype) != hptt.DTYPES[self.dtype]:
@@ -138,10 +142,11 @@ class Contraction:
         self._check_tensors(A, B, C)
         ws = self.workspace()
         st = self._lib.hptt_contraction_exec(
-            self._handle, ctypes.c_void_p(A.data_ptr()), ctypes.c_void_p(B.data_ptr()),
-            ctypes.c_void_p(C.data_ptr()), ctypes.c_void_p(0 if ws is None else ws.data_ptr()),
-            0 if ws is None else ws.numel(), ctypes.c_void_p(hptt._stream(stream)))
-        self._raise(st, "hptt_contraction_exec")
+            self._handle, A.data_ptr(), B.data_ptr(), C.data_ptr(),
+            0 if ws is None else ws.data_ptr(), 0 if ws is None else ws.numel(),
+            hptt._stream(stream))
+        if st != hptt.SUCCESS:
+            self._raise(st, "hptt_contraction_exec")
 
     def exec_no_alloc(self, A, B, C, stream=None):
         """Queue the contraction on `stream` with the library's own device

@@ -242,6 +242,13 @@ class Plan:
                                                self.beta, DTYPES[self.dtype], ctypes.byref(options))
         _check(st, "hptt_create_plan")
         self._handle = handle
+        # what every exec checks its tensors against; a plan never changes
+        info = PlanInfo()
+        _check(self._lib.hptt_plan_info(handle, ctypes.byref(info)), "hptt_plan_info")
+        self._need = {"A": info.footprint_a, "B": info.footprint_b}
+        self._compact = self.outer_size_a is None and self.outer_size_b is None
+        self._torch_dtype = None  # set by the first tensor checked
+        self._exec = getattr(self._lib, "hptt_exec", None)  # None: a plan-only library
 
     @property
     def handle(self) -> ctypes.c_void_p:
@@ -277,16 +284,11 @@ class Plan:
         if not isinstance(A, int):
             self._check_tensor(A, "A")
             self._check_tensor(B, "B")
-        if stream is None:
-            import torch
-            stream = torch.cuda.current_stream().cuda_stream
-        elif not isinstance(stream, int):
-            stream = stream.cuda_stream
-        st = self._lib.hptt_exec(self._handle, ctypes.c_void_p(a), ctypes.c_void_p(b),
-                                 ctypes.c_void_p(stream))
-        if st == HIP_ERROR:
-            raise HpttError(st, f"hptt_exec (hipError {self._lib.hptt_last_hip_error()})")
-        _check(st, "hptt_exec")
+        st = self._exec(self._handle, a, b, _stream(stream))
+        if st != SUCCESS:
+            if st == HIP_ERROR:
+                raise HpttError(st, f"hptt_exec (hipError {self._lib.hptt_last_hip_error()})")
+            _check(st, "hptt_exec")
 
     def launcher(self, A_ptr: int, B_ptr: int, stream: int):
         """A zero-argument callable that queues this plan on fixed device
@@ -303,13 +305,13 @@ class Plan:
     def _check_tensor(self, t, name):
         if not t.is_cuda:
             raise ValueError(f"{name} must be a device tensor")
-        info = self.info
-        need = info["footprint_a"] if name == "A" else info["footprint_b"]
-        if not t.is_contiguous() or t.numel() < need or (
-                self.outer_size_a is None and self.outer_size_b is None and t.numel() != need):
+        need, n = self._need[name], t.numel()
+        if not t.is_contiguous() or n < need or (self._compact and n != need):
             raise ValueError(f"{name} must be contiguous and cover {need} elements")
-        if _dtype_id(t.dtype) != DTYPES[self.dtype]:
-            raise ValueError(f"{name} has dtype {t.dtype}, plan is {self.dtype}")
+        if t.dtype is not self._torch_dtype:
+            if _dtype_id(t.dtype) != DTYPES[self.dtype]:
+                raise ValueError(f"{name} has dtype {t.dtype}, plan is {self.dtype}")
+            self._torch_dtype = t.dtype
 
     def __del__(self):
         if getattr(self, "_handle", None) is not None and self._handle.value:
@@ -334,10 +336,21 @@ def transpose(A, size_a, perm, alpha=1.0, beta=0.0, B=None, **knobs):
     return B
 
 
+_raw_stream = None  # () -> handle of torch's current stream, set by the first call
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        global _raw_stream
+        if _raw_stream is None:
+            import torch
+            torch.cuda.current_stream()  # initialises torch's GPU state
+            try:  # the handle itself, without a Stream object around it
+                raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+                _raw_stream = lambda: raw(device())
+            except AttributeError:
+                _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        return _raw_stream()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
