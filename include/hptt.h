@@ -118,8 +118,8 @@ typedef struct {
                               those extents are not whole lines and the usual
                               B run is not or is long, 1 = wherever they
                               apply, 2 = never.  STREAM: B (compact) walked as
-                              one flat range of whole vectors, A read element
-                              by element: 0 = where the row walk would move
+                              one flat range of whole vectors, A read from any
+                              element boundary: 0 = where the row walk would move
                               one element per access (odd row lengths), or two
                               fp32 elements when beta != 0, 1 = wherever B is
                               compact, 2 = never */

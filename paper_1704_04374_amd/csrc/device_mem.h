@@ -41,11 +41,13 @@ struct DeviceMem {
     // V consecutive elements from any element boundary: one global_load of
     // V*sizeof(T) bytes at a dword-aligned address (gfx950 serves those
     // in both of its alignment modes).
-    template <typename T, int V>
+    template <typename T, int V, bool NT>
     __device__ __forceinline__ static Vec<T, V> ldu(const T* p, int64_t off) {
-        Vec<T, V> r;
-        __builtin_memcpy(&r, p + off, sizeof(r));
-        return r;
+        return ldub<T, V, NT>(p + off, 0);
+    }
+    template <bool NT, typename T, int V>
+    __device__ __forceinline__ static void stu(T* p, int64_t off, const Vec<T, V>& v) {
+        stub<NT, T, V>(p + off, 0, v);
     }
     // Byte-offset accesses: p is the same for the whole wave, off a lane's own
     // 32-bit byte offset (a scalar base and one vector register).  ldub and stub

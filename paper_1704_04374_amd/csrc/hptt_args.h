@@ -205,8 +205,9 @@ struct StreamArgs {
     uint32_t numItems[3];       // numRows * W for V = 1, 2, 4 (flat: ceil(numel / V))
     // Flat walk (B compact, numel < 2^32): item i is B's vector i, elements
     // [i*V, i*V + V) of the flat B range, whatever the row length; its
-    // elements come from at most two rows (rowLen >= V), read from A one by
-    // one.  L divides a flat B offset into (row, column).
+    // elements come from at most two rows (rowLen >= V).  1: by a table of row
+    // offsets (stream_flat_items), 2: each lane on its own (stream_items_flat).
+    // L divides a flat B offset into (row, column).
     int32_t flatB;
     // L > 0: the workgroups one XCD receives take block numbers 2^L
     // consecutive at a time (xcd_group_map), so that blocks reading

@@ -991,15 +991,101 @@ __host__ __device__ inline int64_t stream_row_a(const StreamArgs& g, uint32_t r)
 
 // Flat walk of kernel S (g.flatB): item i is B's vector i, so every B access
 // is a whole vector even when the row length is not a multiple of the width
-// (rows of 63 fp32 would otherwise move one element per access).  The row
-// split is done once per vector (twice when the vector crosses into the next
-// row); A is read with ordinary loads, since its rows start anywhere: fp32
-// with B only written takes one element-aligned vector load where the
-// vector's elements lie in one row (MI355X, rows of 55-213 elements +27 to
-// +35 %); elsewhere, and where a vector crosses into the next row, element by
-// element (the vector load lost 2-6 % when B is read, and with fp64).  Same
-// lane map as stream_items.
+// (rows of 63 fp32 would otherwise move one element per access).  A workgroup
+// takes kFlatItems vectors per lane, consecutive in B; the A offsets of the
+// rows they lie in are split once per workgroup into an LDS table (MI355X,
+// rows of 75 fp32: splitting them in every lane, and reading the vectors that
+// cross into the next row element by element, took 135 VALU instructions and
+// 5 loads per 16-byte vector and wave).  A vector is read from A at any
+// element boundary, as the last V elements of its row when it crosses into
+// the next, and then completed from the first V of that one.  Two vectors per
+// lane: on rows of 75, 213 and 498 fp32 one takes 77.4, 75.8 and 72.3 us, two
+// 72.9, 67.0 and 67.0, four 74.2, 68.7 and 68.1 (split in every lane: 79.0,
+// 74.3 and 72.0); fp64 rows of 63 71.6 -> 64.4.
+constexpr int kFlatItems = 2;
+
+// Rows that a workgroup's vectors can touch.
+template <int V>
+__host__ __device__ inline int stream_flat_rows(uint32_t rowLen) {
+    return int((uint32_t(kBlock * kFlatItems * V) + rowLen - 1) / rowLen) + 1;
+}
+
+// rowA[i] = A offset of the i-th row from the one that holds element first * V
+// (the last row's beyond the tensor).
+template <class Mem, int V>
+__host__ __device__ inline void stream_flat_table(const StreamArgs& g, uint32_t first, int tid,
+                                                  int64_t* rowA) {
+    const int rows = stream_flat_rows<V>(g.L.d);
+    const uint32_t r0 = fast_div(first * V, g.L), last = uint32_t(g.numRows) - 1;
+    for (int i = tid; i < rows; i += kBlock)
+        Mem::template lds_st<int64_t>(rowA, i, stream_row_a(g, imin(r0 + uint32_t(i), last)));
+}
+
 template <class Mem, typename T, int V, int MODE, int HINT>
+__host__ __device__ inline void stream_flat_items(const StreamArgs& g, uint32_t first, int tid,
+                                                  const T* A, T* B, const int64_t* rowA, T alpha,
+                                                  T beta) {
+    const uint32_t numel = uint32_t(g.numRows * g.rowLen);
+    const int rowLen = int(g.L.d);
+    const uint32_t r0 = fast_div(first * V, g.L);
+    // the loads first, then what the crossing vectors still need
+    Vec<T, V> x[kFlatItems], w[kFlatItems], y[kFlatItems];
+    int k[kFlatItems];  // elements that lie in the vector's first row
+#pragma unroll
+    for (int u = 0; u < kFlatItems; ++u) {
+        const uint32_t at = (first + uint32_t(u * kBlock + tid)) * V;
+        k[u] = V;
+        if (at + V <= numel) {
+            const uint32_t r = fast_div(at, g.L);
+            const int c = int(at - r * g.L.d);
+            k[u] = rowLen - c;
+            x[u] = Mem::template ldu<T, V, false>(
+                A, Mem::template lds_ld<int64_t>(rowA, r - r0) + imin(c, rowLen - V));
+            if (k[u] < V)
+                w[u] = Mem::template ldu<T, V, false>(
+                    A, Mem::template lds_ld<int64_t>(rowA, r - r0 + 1));
+            if (MODE == kAxpby) y[u] = Mem::template ldu<T, V, (HINT & kNtStore) != 0>(B, at);
+        } else if (at < numel) {  // the tensor's last elements, in its last row
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (at + e < numel) {
+                    x[u].v[e] = Mem::template ld1<T>(
+                        A, Mem::template lds_ld<int64_t>(rowA, fast_div(at + e, g.L) - r0) +
+                               int64_t((at + e) % uint32_t(rowLen)));
+                    if (MODE == kAxpby) y[u].v[e] = Mem::template ld1<T>(B, at + e);
+                }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kFlatItems; ++u) {
+        const uint32_t at = (first + uint32_t(u * kBlock + tid)) * V;
+        Vec<T, V> z;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            T a = x[u].v[e];
+#pragma unroll
+            for (int j = 1; j < V; ++j)
+                if (k[u] == j) a = e < j ? x[u].v[V - j + e] : w[u].v[e - j];
+            z.v[e] = update<MODE>(a, MODE == kAxpby ? y[u].v[e] : T(0), alpha, beta);
+        }
+        if (at + V <= numel) {
+            Mem::template stu<(HINT & kNtStore) != 0, T, V>(B, at, z);
+        } else if (at < numel) {
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (at + e < numel) Mem::template st1<false, T>(B, at + e, z.v[e]);
+        }
+    }
+}
+
+// Flat walk of long rows where B is read (g.flatB = 2): one vector per lane,
+// each splitting its own row and reading A element by element.  With beta =
+// 1 this stays ahead of the table above (MI355X, fp32 rows of 213, 498 and
+// 25001: 93.0, 92.2 and 92.8 us against 95.7, 96.0 and 96.3; fp64 rows of 63
+// and 95: 86.5 and 161.9 against 87.7 and 166.5; measured, not explained);
+// shorter rows gain from the table (17: 138.7 -> 114.3 us, 42: 107.4 -> 101.3,
+// 75: 100.3 -> 98.2, fp64 33: 81.6 -> 80.0).
+template <class Mem, typename T, int V, int HINT>
 __host__ __device__ inline void stream_items_flat(const StreamArgs& g, uint32_t first, int tid,
                                                   const T* A, T* B, T alpha, T beta) {
     const uint32_t numItems = g.numItems[log2_width(V)];
@@ -1019,23 +1105,16 @@ __host__ __device__ inline void stream_items_flat(const StreamArgs& g, uint32_t 
             const uint32_t r = fast_div(uint32_t(offB[u]), g.L);
             const int c0 = int(uint32_t(offB[u]) - r * g.L.d);
             const int64_t a0 = stream_row_a(g, r);
-            if (sizeof(T) == 4 && MODE != kAxpby && n[u] == V && c0 + V <= rowLen) {
-                // inside one row: one load from wherever the row puts it
-                x[u] = Mem::template ldu<T, V>(A, a0 + c0);
-            } else {
-                const int64_t a1 = c0 + n[u] > rowLen ? stream_row_a(g, r + 1) - rowLen : a0;
+            const int64_t a1 = c0 + n[u] > rowLen ? stream_row_a(g, r + 1) - rowLen : a0;
 #pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (e < n[u])
+                    x[u].v[e] = Mem::template ld1<T>(A, (c0 + e < rowLen ? a0 : a1) + c0 + e);
+            if (n[u] == V) {
+                y[u] = Mem::template ld<T, V, (HINT & kNtStore) != 0>(B, offB[u]);
+            } else {
                 for (int e = 0; e < V; ++e)
-                    if (e < n[u])
-                        x[u].v[e] = Mem::template ld1<T>(A, (c0 + e < rowLen ? a0 : a1) + c0 + e);
-            }
-            if (MODE == kAxpby) {
-                if (n[u] == V) {
-                    y[u] = Mem::template ld<T, V, (HINT & kNtStore) != 0>(B, offB[u]);
-                } else {
-                    for (int e = 0; e < V; ++e)
-                        if (e < n[u]) y[u].v[e] = Mem::template ld1<T>(B, offB[u] + e);
-                }
+                    if (e < n[u]) y[u].v[e] = Mem::template ld1<T>(B, offB[u] + e);
             }
         }
     }
@@ -1045,7 +1124,7 @@ __host__ __device__ inline void stream_items_flat(const StreamArgs& g, uint32_t 
         Vec<T, V> z;
 #pragma unroll
         for (int e = 0; e < V; ++e)
-            z.v[e] = update<MODE>(x[u].v[e], MODE == kAxpby ? y[u].v[e] : T(0), alpha, beta);
+            z.v[e] = update<kAxpby>(x[u].v[e], y[u].v[e], alpha, beta);
         if (n[u] == V) {
             Mem::template st<(HINT & kNtStore) != 0, T, V>(B, offB[u], z);
         } else {

@@ -25,15 +25,36 @@ __global__ __launch_bounds__(kBlock) void stream_kernel(const T* __restrict__ A,
     const uint64_t items = g.numItems[log2_width(V)];
     const uint32_t blk = g.xcdGroupLog ? xcd_group_map(blockIdx.x, gridDim.x, uint32_t(g.xcdGroupLog))
                                        : blockIdx.x;
-    if (g.flatB) {
-        for (uint64_t first = uint64_t(blk) * per; first < items; first += step)
-            stream_items_flat<DeviceMem, T, V, MODE, HINT>(g, uint32_t(first), int(threadIdx.x), A,
-                                                           B, alpha, beta);
-        return;
+    if constexpr (MODE == kAxpby) {
+        if (g.flatB) {
+            for (uint64_t first = uint64_t(blk) * per; first < items; first += step)
+                stream_items_flat<DeviceMem, T, V, HINT>(g, uint32_t(first), int(threadIdx.x), A, B,
+                                                         alpha, beta);
+            return;
+        }
     }
     for (uint64_t first = uint64_t(blk) * per; first < items; first += step)
         stream_items<DeviceMem, T, V, MODE, HINT>(g, uint32_t(first), int(threadIdx.x), A, B, alpha,
                                                   beta);
+}
+
+template <typename T, int V, int MODE, int HINT>
+__global__ __launch_bounds__(kBlock) void stream_flat_kernel(const T* __restrict__ A,
+                                                             T* __restrict__ B, const StreamArgs g,
+                                                             T alpha, T beta) {
+    extern __shared__ int64_t rowA[];
+    constexpr uint64_t per = uint64_t(kBlock) * kFlatItems;
+    const uint64_t step = uint64_t(gridDim.x) * per, items = g.numItems[log2_width(V)];
+    const uint32_t blk = g.xcdGroupLog ? xcd_group_map(blockIdx.x, gridDim.x, uint32_t(g.xcdGroupLog))
+                                       : blockIdx.x;
+    const int tid = int(threadIdx.x);
+    for (uint64_t first = uint64_t(blk) * per; first < items; first += step) {
+        if (first != uint64_t(blk) * per) __syncthreads();  // the previous table's reads are done
+        stream_flat_table<DeviceMem, V>(g, uint32_t(first), tid, rowA);
+        __syncthreads();
+        stream_flat_items<DeviceMem, T, V, MODE, HINT>(g, uint32_t(first), tid, A, B, rowA, alpha,
+                                                       beta);
+    }
 }
 
 template <typename T, int V, int MODE, int HINT>
@@ -74,6 +95,19 @@ const void* stream_fn(int v) {
 }
 
 template <typename T, int MODE, int HINT>
+const void* stream_flat_fn(int v) {
+    switch (v) {
+        case 1: return reinterpret_cast<const void*>(&stream_flat_kernel<T, 1, MODE, HINT>);
+        case 2: return reinterpret_cast<const void*>(&stream_flat_kernel<T, 2, MODE, HINT>);
+        case 4:
+            if constexpr (kMaxVec<T> >= 4)
+                return reinterpret_cast<const void*>(&stream_flat_kernel<T, 4, MODE, HINT>);
+            return nullptr;
+    }
+    return nullptr;
+}
+
+template <typename T, int MODE, int HINT>
 const void* axpby_fn(int v) {
     switch (v) {
         case 1: return reinterpret_cast<const void*>(&axpby_kernel<T, 1, MODE, HINT>);
@@ -97,8 +131,10 @@ const void* generic_fn(bool big) {
 template <typename T, int MODE, int HINT>
 const void* select(const hptt_plan_s* p, int va, int vb) {
     switch (p->info.kernel) {
-        // the flat walk reads A element by element: only B's width counts
         case HPTT_KERNEL_STREAM:
+            // the flat walk by table moves the plan's width at any element
+            // boundary; the other reads A element by element: only B's width counts
+            if (p->stream.flatB == 1) return stream_flat_fn<T, MODE, HINT>(p->info.vec_b);
             return stream_fn<T, MODE, HINT>(p->stream.flatB || va >= vb ? vb : va);
         case HPTT_KERNEL_AXPBY: return axpby_fn<T, MODE, HINT>(va < vb ? va : vb);
         case HPTT_KERNEL_GENERIC:
@@ -237,7 +273,13 @@ hptt_status_t launch(const hptt_plan_s* p, const void* A, void* B, hipStream_t s
                     return stream_slabs<T>(p, fn, a, b, v, alpha, beta, stream);
             }
             args[2] = const_cast<StreamArgs*>(&p->stream);
-            lds = size_t(in.lds_bytes);
+            if (p->stream.flatB == 1) {
+                const uint32_t len = p->stream.L.d;
+                const int rows = in.vec_b == 4   ? stream_flat_rows<4>(len)
+                                 : in.vec_b == 2 ? stream_flat_rows<2>(len)
+                                                 : stream_flat_rows<1>(len);
+                lds = size_t(rows) * sizeof(int64_t);
+            }
             break;
         case HPTT_KERNEL_AXPBY: args[2] = &numel; break;
         case HPTT_KERNEL_GENERIC: args[2] = const_cast<GenericArgs*>(&p->generic); break;

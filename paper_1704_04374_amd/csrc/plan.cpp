@@ -1079,24 +1079,24 @@ bool setup_stream(const Fused& f, int elem, const hptt_options_t& opt, StreamArg
     const int32_t v = vec_width(gran, elem, opt.max_vec);
     // Flat walk: B compact (its rows back to back), and rows that would move
     // one element per access (odd row lengths), or two fp32 elements; every
-    // B access is then a whole vector.  MI355X, fp32 rows of 55-213
-    // elements: +13 to +24 % (e.g. 63-element rows 3.11 -> 3.65 TB/s with
-    // beta = 0, 4.25 -> 5.27 with beta = 1), and +27 to +35 % more with beta
-    // = 0 since A is read a vector at a time there; fp32 rows of 42 and 66
-    // (two elements per access) +12 % and +9 % with beta = 1, and with beta =
-    // 0 rows of 42 and 498 +11 % and +14 % (they lost 7-9 % while A was read
-    // element by element); fp64 rows of 33-211 elements +5 to +19 % with beta
-    // = 0, +2 to +14 % on three of four with beta = 0.5 (-3 % on rows of 95).
+    // B access is then a whole vector.  MI355X against the row walk: fp32 rows
+    // of 63 and 75 with beta = 0 128 -> 75 and 118 -> 73 us per 400 MB; with
+    // beta = 1 +13 to +24 %; fp32 rows of two-element accesses +10 to +35 %; fp64
+    // rows of 33-211 elements +10 to +29 % with beta = 0, +2 to +14 % on three
+    // of four with beta = 0.5 (-3 % on rows of 95).
     const int32_t vWide = vec_width(0, elem, opt.max_vec);
     bool compactB = f.M < 2 || f.sB[f.p[1]] == s.rowLen;
     for (int k = 1; k + 1 < f.M; ++k)
         compactB = compactB && f.sB[f.p[k + 1]] == f.sB[f.p[k]] * f.n[f.p[k]];
     const int64_t numel = rows * s.rowLen;
-    if (opt.flat_runs != 2 && compactB && numel < (int64_t(1) << 32) - int64_t(kBlock) * kMaxItems &&
+    // (a workgroup counts elements up to its own size past the last one)
+    if (opt.flat_runs != 2 && compactB &&
+        numel < (int64_t(1) << 32) - 2 * int64_t(kBlock) * kFlatItems * vWide &&
         s.rowLen >= vWide &&
         (opt.flat_runs == 1 ||
          (v < vWide && (v == 1 || (elem == 4 && v == 2))))) {
-        s.flatB = 1;
+        // by table, or with each lane splitting its own row (kernel_body.h)
+        s.flatB = info.mode == kAxpby && s.rowLen * elem > 320 ? 2 : 1;
         set_div(s.L, s.rowLen);
         for (int w = 0; w < 3; ++w) s.numItems[w] = uint32_t((numel + (1 << w) - 1) >> w);
         info.vec_a = info.vec_b = vWide;
@@ -1566,7 +1566,9 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
             if (opt.kernel == HPTT_KERNEL_STREAM) return HPTT_ERROR_UNSUPPORTED;
             k = HPTT_KERNEL_GENERIC;
         } else {
-            const int64_t per = int64_t(kBlock) * items_per_lane(elem, info.vec_a);
+            const int64_t per = int64_t(kBlock) * (plan->stream.flatB == 1
+                                                       ? kFlatItems
+                                                       : items_per_lane(elem, info.vec_a));
             int64_t grid = (info.tiles + per - 1) / per;
             if (grid > (int64_t(1) << 30)) grid = int64_t(1) << 30;
             info.grid = grid < maxBlocks ? grid : maxBlocks;
@@ -1595,7 +1597,7 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
     // when the neighbour wants it, and a partly written B line stored
     // non-temporally reaches HBM as a partial write instead of being merged
     // with the neighbour's part in L2 (2-3.5x slower on MI355X).
-    // (the flat walk of kernel S reads A element by element, lines shared
+    // (the flat walk of kernel S reads A off the vector grid, lines shared
     // between neighbouring vectors)
     const bool loadOk = (k != HPTT_KERNEL_TILE || plan->tile.alignedA) &&
                         !(k == HPTT_KERNEL_STREAM && plan->stream.flatB);

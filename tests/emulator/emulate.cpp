@@ -135,7 +135,11 @@ struct HostMem {
     }
     static void wait_ld_lds() {}
     static int wave_uniform(int x) { return x; }
-    template <typename T, int V>
+    template <bool NT, typename T, int V>
+    static void stu(T* p, int64_t off, const hptt::Vec<T, V>& v) {
+        for (int e = 0; e < V; ++e) st1<NT, T>(p, off + e, v.v[e]);
+    }
+    template <typename T, int V, bool NT>
     static hptt::Vec<T, V> ldu(const T* p, int64_t off) {
         hptt::Vec<T, V> r;
         memset(&r, 0, sizeof(r));
@@ -205,7 +209,7 @@ struct HostMem {
     }
     template <typename T, int V, bool NT>
     static hptt::Vec<T, V> ldub(const T* p, uint32_t off) {
-        return ldu<T, V>(plus(p, off), 0);
+        return ldu<T, V, NT>(plus(p, off), 0);
     }
     template <typename T, int V, bool NT>
     static hptt::Vec<T, V> ldb(const T* p, uint32_t off) {
@@ -451,12 +455,42 @@ void emu_stream_launch(const hptt::StreamArgs& g, uint64_t grid, const T* A, T* 
         for (uint64_t first = blk * per;
              first < g.numItems[log2_width(V)] && S->errors == 0; first += step)
             for (int tid = 0; tid < kBlock; ++tid) {
-                if (g.flatB)
-                    stream_items_flat<HostMem, T, V, MODE, NT>(g, uint32_t(first), tid, A, B, alpha,
-                                                               beta);
-                else
-                    stream_items<HostMem, T, V, MODE, NT>(g, uint32_t(first), tid, A, B, alpha, beta);
+                if constexpr (MODE == kAxpby) {
+                    if (g.flatB) {
+                        stream_items_flat<HostMem, T, V, NT>(g, uint32_t(first), tid, A, B, alpha,
+                                                             beta);
+                        continue;
+                    }
+                }
+                stream_items<HostMem, T, V, MODE, NT>(g, uint32_t(first), tid, A, B, alpha, beta);
             }
+    }
+}
+
+// Mirrors stream_flat_kernel in kernels.hip.
+template <typename T, int V, int MODE>
+void emu_stream_flat(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
+    using namespace hptt;
+    const StreamArgs& g = p->stream;
+    const T alpha = T(p->alpha), beta = T(p->beta);
+    const int64_t bytes = int64_t(stream_flat_rows<V>(g.L.d)) * int64_t(sizeof(int64_t));
+    S->lds.assign(size_t(bytes), 0);
+    S->written.assign(size_t(bytes), 0);
+    int64_t* rowA = reinterpret_cast<int64_t*>(S->lds.data());
+    const uint64_t grid = uint64_t(p->info.grid), per = uint64_t(kBlock) * kFlatItems;
+    for (uint64_t blk0 = 0; blk0 < grid && S->errors == 0; blk0 += uint64_t(blockStride)) {
+        const uint64_t blk =
+            g.xcdGroupLog ? xcd_group_map(uint32_t(blk0), uint32_t(grid), uint32_t(g.xcdGroupLog))
+                          : blk0;
+        for (uint64_t first = blk * per; first < g.numItems[log2_width(V)] && S->errors == 0;
+             first += grid * per) {
+            clear_written(0, bytes);
+            for (int tid = 0; tid < kBlock; ++tid)
+                stream_flat_table<HostMem, V>(g, uint32_t(first), tid, rowA);
+            for (int tid = 0; tid < kBlock; ++tid)
+                stream_flat_items<HostMem, T, V, MODE, 0>(g, uint32_t(first), tid, A, B, rowA, alpha,
+                                                          beta);
+        }
     }
 }
 
@@ -467,6 +501,12 @@ void emu_stream(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
     using namespace hptt;
     const StreamArgs& g = p->stream;
     const T alpha = T(p->alpha), beta = T(p->beta);
+    if (g.flatB == 1) {  // at the plan's width, whatever the pointers
+        if (p->info.vec_b == 1) emu_stream_flat<T, 1, MODE>(p, A, B, blockStride);
+        else if (p->info.vec_b == 2) emu_stream_flat<T, 2, MODE>(p, A, B, blockStride);
+        else if constexpr (sizeof(T) == 4) emu_stream_flat<T, 4, MODE>(p, A, B, blockStride);
+        return;
+    }
     if (g.flatB || g.numItems[log2_width(V)] != 0) {
         emu_stream_launch<T, V, MODE, NT>(g, uint64_t(p->info.grid), A, B, alpha, beta,
                                           blockStride);
