@@ -148,7 +148,8 @@ typedef struct {
 /* What the plan builder decided; for inspection and tests.  Where
  * hptt_describe_plan's line ends in "matrix=...", hptt_exec runs the
  * problem with flattened two-dimensional tiles of that size instead of the
- * TILE plan described here, which hptt_create_plan_ex's options still give. */
+ * TILE plan described here, which hptt_create_plan_ex's options still give;
+ * "permute=..." likewise, with shared-run tiles that stay in one workgroup. */
 typedef struct {
     int32_t ndim;                      /* rank after dropping extent-1 indices and fusing */
     int64_t size[HPTT_MAX_DIMS];       /* fused extents of A */

@@ -26,8 +26,8 @@ CONTRACT_SOURCES = ["contract.hip", "contract_direct.hip", "contract_direct_plan
 
 ARCH = "gfx950"
 # the tile kernel instantiations are split over several files so they compile in parallel
-SOURCES = ["tile_matrix.hip", "tile_f32_fast.hip", "tile_f32_shifted.hip", "tile_f32_general.hip", "tile_shared.hip",
-           "tile_direct.hip", "tile_f64.hip", "kernels.hip",
+SOURCES = ["tile_matrix.hip", "tile_perm.hip", "tile_f32_fast.hip", "tile_f32_shifted.hip",
+           "tile_f32_general.hip", "tile_shared.hip", "tile_direct.hip", "tile_f64.hip", "kernels.hip",
            "yardstick.hip", "api.cpp", "plan.cpp", "autotune.cpp"]
 
 # -ffp-contract=off: alpha*a + beta*b is two roundings and an add, never an

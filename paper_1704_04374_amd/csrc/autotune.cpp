@@ -53,9 +53,10 @@ bool same_plan(const hptt_plan_s& a, const hptt_plan_s& b) {
         a.info.vec_a != b.info.vec_a || a.info.vec_b != b.info.vec_b)
         return false;
     if (a.info.kernel == HPTT_KERNEL_TILE)
-        return a.matrix.use == b.matrix.use &&
-               (a.matrix.use ? memcmp(&a.matrix, &b.matrix, sizeof(a.matrix)) == 0
-                             : memcmp(&a.tile, &b.tile, sizeof(a.tile)) == 0);
+        return a.matrix.use == b.matrix.use && a.perm.use == b.perm.use &&
+               (a.perm.use ? memcmp(&a.perm, &b.perm, sizeof(a.perm)) == 0
+                : a.matrix.use ? memcmp(&a.matrix, &b.matrix, sizeof(a.matrix)) == 0
+                               : memcmp(&a.tile, &b.tile, sizeof(a.tile)) == 0);
     if (a.info.kernel == HPTT_KERNEL_STREAM)  // row or flat walk, XCD groups
         return memcmp(&a.stream, &b.stream, sizeof(a.stream)) == 0;
     return true;

@@ -118,6 +118,13 @@ struct DeviceMem {
         __builtin_amdgcn_s_waitcnt(0);
 #endif
     }
+    // Makes x unknown to the compiler, so that what follows from it is worked
+    // out where it is used instead of being kept in registers around a loop.
+    __device__ __forceinline__ static void opaque(uint32_t& x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(x));
+#endif
+    }
     // A value the whole wave holds, kept in a scalar register.
     __device__ __forceinline__ static int wave_uniform(int x) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -193,6 +193,29 @@ struct MatrixArgs {
     int64_t gStrideA[kMaxDims], gStrideB[kMaxDims];  // bytes
 };
 
+// Kernel P: the shared-run tiles of kernel T (TileArgs::shared) for
+// workgroups that take several tiles each (perm_body.h).
+constexpr int kPermDims = 8;
+struct PermArgs {
+    int32_t use;           // 1: hptt_exec launches kernel P instead of kernel T
+    int32_t hints;
+    int32_t vectors;       // vectors per lane: one of kPermVectors
+    int32_t ldsBytes;
+    int32_t runA, rows, pitch, runB, colsS;
+    int32_t loads, stores; // vectors of a tile on each side
+    FastDiv vecsA, vecsB;  // vectors per row and per column
+    int32_t nR, nC, nO, nG;
+    uint32_t numTiles, grid;
+    int32_t skew, xcdGroupLog;
+    int32_t gChunkC, gChunkR;
+    int32_t cInner, cChunk, cLast, cInnerS;
+    int32_t rInner, rChunk, rLast, rInnerL;
+    FastDiv rExt[kPermDims], cExt[kPermDims], oExt[kPermDims], gExt[kPermDims];
+    uint32_t rStrideA[kPermDims], cStrideB[kPermDims];  // bytes
+    uint32_t cLds[kPermDims], oLds[kPermDims];          // elements
+    int64_t gStrideA[kPermDims], gStrideB[kPermDims];   // bytes
+};
+
 // Kernel S: A's stride-1 index is also B's.  Each "row" is one full run of
 // that index, contiguous in both tensors.  Work item i = r*W + c is vector c
 // of row r (rows in B order, W vectors per row), so consecutive lanes write

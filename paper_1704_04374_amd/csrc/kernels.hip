@@ -216,12 +216,36 @@ hptt_status_t launch_matrix(const hptt_plan_s* p, const T* A, T* B, hipStream_t 
     return HPTT_SUCCESS;
 }
 
+// Kernel P: any element-aligned pointers.
+template <typename T>
+hptt_status_t launch_perm(const hptt_plan_s* p, const T* A, T* B, hipStream_t stream) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(A), pb = reinterpret_cast<uintptr_t>(B);
+    const PermArgs& g = p->perm;
+    int hints = g.hints;  // as in launch: none where a base is off the lines
+    if (pb % 128 != 0) hints = 0;
+    if (pa % 128 != 0) hints &= ~kNtLoad;
+    const void* fn = sizeof(T) == 4 ? perm_kernel_f32(g.vectors, p->info.mode, hints)
+                                    : perm_kernel_f64(g.vectors, p->info.mode, hints);
+    if (!fn) return HPTT_ERROR_INVALID_ARGUMENT;
+    T alpha = T(p->alpha), beta = T(p->beta);
+    void* args[5] = {&A, &B, const_cast<PermArgs*>(&g), &alpha, &beta};
+    const hipError_t err =
+        hipLaunchKernel(fn, dim3(g.grid), dim3(kBlock), args, size_t(g.ldsBytes), stream);
+    if (err != hipSuccess) {
+        g_last_hip_error = int32_t(err);
+        return HPTT_ERROR_HIP;
+    }
+    return HPTT_SUCCESS;
+}
+
 template <typename T>
 hptt_status_t launch(const hptt_plan_s* p, const void* A, void* B, hipStream_t stream) {
     const hptt_plan_info_t& in = p->info;
     const int elem = int(sizeof(T));
     if (in.kernel == HPTT_KERNEL_TILE && p->matrix.use)
         return launch_matrix<T>(p, static_cast<const T*>(A), static_cast<T*>(B), stream);
+    if (in.kernel == HPTT_KERNEL_TILE && p->perm.use)
+        return launch_perm<T>(p, static_cast<const T*>(A), static_cast<T*>(B), stream);
     const uintptr_t pa = reinterpret_cast<uintptr_t>(A), pb = reinterpret_cast<uintptr_t>(B);
     // The tile kernel keeps its widths and shifts its runs onto the vector
     // grid of the actual pointers; the others narrow to the pointers' alignment.
@@ -330,6 +354,7 @@ hptt_status_t hptt_load_kernels(void) {
                          tile_kernel_f32(kShared, kCopy, 0, 1, 1, kBlock),
                          tile_kernel_f64(kFast, kCopy, 0, 1, 1, kBlock),
                          matrix_kernel_f32(0, kCopy, 0), matrix_kernel_f64(0, kCopy, 0),
+                         perm_kernel_f32(1, kCopy, 0),
                          stream_fn<float, kCopy, 0>(1)};
     for (const void* f : fns) {
         if (!f) continue;

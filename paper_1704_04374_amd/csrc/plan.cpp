@@ -996,6 +996,76 @@ void choose_matrix(const Fused& f, int elem, int64_t numel, const TileArgs& t,
     g.hints = (store ? kNtStore : 0) | (load ? kNtLoad : 0);
 }
 
+// Kernel P for the shared-run tiles of t.  False where its packed numbers
+// (16 bits), 32-bit offsets or register vectors do not hold them.
+const int kPermVectors[] = {1, 2, 3, 5};
+// Four workgroups per CU: as many as 95 VGPRs (5 vectors per lane) and 20 KB of
+// LDS leave room for.  With fewer vectors more would fit and were slower
+// (fp32 2925x1207x2x7, perm 2,0,3,1: 86 us with three per CU, 96 with seven).
+constexpr int64_t kPermGrid = 1024;
+
+bool setup_perm(const TileArgs& t, int elem, PermArgs& g) {
+    memset(&g, 0, sizeof(g));
+    const int V = 16 / elem;
+    if (!t.shared || t.nR > kPermDims || t.nC > kPermDims || t.nO > kPermDims || t.nG > kPermDims)
+        return false;
+    if (t.runA < V || t.runB < V || t.xcdSplit || t.skew > 1) return false;
+    const int64_t data = int64_t(t.subRows) * t.pitch;
+    const int64_t wa = (t.runA + V - 1) / V, wb = (t.runB + V - 1) / V;
+    if (data >= (1 << 16) || t.runA >= (1 << 16) || t.runB >= (1 << 16)) return false;
+    const int64_t limit = int64_t(1) << 31;
+    if (t.cLast >= limit || t.rLast >= limit) return false;
+    g.loads = int32_t(wa * t.subRows);
+    g.stores = int32_t(wb * t.nColS);
+    const int64_t need = (std::max(g.loads, g.stores) + kBlock - 1) / kBlock;
+    for (int n : kPermVectors)
+        if (g.vectors == 0 && need <= n) g.vectors = n;
+    if (g.vectors == 0) return false;
+    g.ldsBytes = int32_t((data * elem + 15) / 16 * 16);
+    if (g.ldsBytes > kLdsMax) return false;
+    g.runA = int32_t(t.runA);
+    g.rows = t.subRows;
+    g.pitch = t.pitch;
+    g.runB = int32_t(t.runB);
+    g.colsS = t.nColS;
+    set_div(g.vecsA, wa);
+    set_div(g.vecsB, wb);
+    g.nR = t.nR, g.nC = t.nC, g.nO = t.nO, g.nG = t.nG;
+    // offsets of lanes beyond a tile's vectors wrap; they are never used
+    int64_t spanA = t.runA, spanB = t.runB;
+    for (int k = 0; k < t.nR; ++k) {
+        g.rExt[k] = t.rExt[k];
+        spanA += (int64_t(t.rExt[k].d) - 1) * t.rStrideA[k];
+        g.rStrideA[k] = uint32_t(t.rStrideA[k] * elem);
+    }
+    for (int k = 0; k < t.nC; ++k) {
+        g.cExt[k] = t.cExt[k];
+        spanB += (int64_t(t.cExt[k].d) - 1) * t.cStrideB[k];
+        g.cStrideB[k] = uint32_t(t.cStrideB[k] * elem);
+        g.cLds[k] = uint32_t(t.cLds[k]);
+    }
+    if (spanA * elem >= 2 * limit || spanB * elem >= 2 * limit) return false;
+    for (int k = 0; k < t.nO; ++k) {
+        g.oExt[k] = t.oExt[k];
+        g.oLds[k] = uint32_t(t.oLds[k]);
+    }
+    for (int k = 0; k < t.nG; ++k) {
+        g.gExt[k] = t.gExt[k];
+        g.gStrideA[k] = t.gStrideA[k] * elem;
+        g.gStrideB[k] = t.gStrideB[k] * elem;
+    }
+    g.numTiles = t.numTiles;
+    g.skew = t.skew;
+    g.xcdGroupLog = t.xcdGroupLog;
+    g.gChunkC = t.gChunkC, g.gChunkR = t.gChunkR;
+    g.cInner = int32_t(t.cInner), g.cChunk = int32_t(t.cChunk), g.cLast = int32_t(t.cLast);
+    g.cInnerS = t.cInnerS;
+    g.rInner = int32_t(t.rInner), g.rChunk = int32_t(t.rChunk), g.rLast = int32_t(t.rLast);
+    g.rInnerL = t.rInnerL;
+    g.grid = uint32_t(std::min<int64_t>(g.numTiles, kPermGrid));
+    return true;
+}
+
 // Score of a tile shape for the choice between disjoint and shared runs:
 // the bytes of each run up to 512 (a run shorter than a few lines wastes
 // most of each HBM burst), then the tile up to kMinTileBytes, and a penalty
@@ -1009,8 +1079,9 @@ double tile_score(int64_t runA, int64_t runB, int64_t tileElems, uint64_t tiles,
 
 // The best shared-run tile over a few pairs of run targets (or the
 // requested ones), by tile_score.
+// With `within` > 0 only tiles of that many LDS bytes.
 bool choose_shared(const Fused& f, int elem, const hptt_options_t& opt, TileArgs& best,
-                    hptt_plan_info_t& bestInfo, double& bestScore) {
+                    hptt_plan_info_t& bestInfo, double& bestScore, int64_t within = 0) {
     static const int64_t aBytes[] = {512, 1024, 2048, 4096, 8192, 16384};
     static const int64_t bBytes[] = {128, 512, 2048, 8192};
     const hptt_plan_info_t base = bestInfo;
@@ -1037,6 +1108,7 @@ bool choose_shared(const Fused& f, int elem, const hptt_options_t& opt, TileArgs
             }
         return fnd;
     };
+    if (within > 0) return search(within, 0, best, bestInfo, bestScore);
     const bool readsB = base.mode == kAxpby;
     bool found = search(readsB ? kSharedLdsBudgetAxpby : kLdsBudget, 0, best, bestInfo, bestScore);
     // With B read, fp32 tiles of one or two rows take the larger budget too
@@ -1054,6 +1126,50 @@ bool choose_shared(const Fused& f, int elem, const hptt_options_t& opt, TileArgs
         }
     }
     return found;
+}
+
+// The tile of kernel P for the shared-run problem of t: t itself, or the best
+// one that its registers hold; false where kernel T is as good.  Up to 12 MB a
+// call is mostly the lanes' index work, which kernel P does once: 1.2-2.2x
+// over 43 drawn problems (8.7-12.3 us -> 4.2-6 below 0.5 MB), slower on none.  The
+// LDS of a tile is 1/200 of the tensor, so that the CUs have one each (0.3-0.5
+// MB: 4.2-5.4 us, against 7.1-10.6 with 20 KB tiles).  Above that, HBM binds:
+//  - fp32 with beta == 0, runs of at least 1 KiB on both sides and two tiles
+//    per workgroup: 90-122 us -> 79-86 at 200 MB (kernel T 82% of the copy
+//    rate at best, kernel P 92%).  Shorter runs are 0-20% slower (2x565x30x1475:
+//    107 -> 126-148 us), fewer tiles leave the last turn of the workgroups
+//    partly empty (20-40 MB: 16.4 -> 18.1 us).
+//  - fp64 halves kernel T's index work per byte, and with beta != 0 twice the
+//    loads in flight matter more: 0.97-1.03x and 0.83-1.1x, so kernel T stays.
+bool choose_perm(const Fused& f, int elem, int64_t numel, const TileArgs& t,
+                 const hptt_plan_info_t& info, PermArgs& g) {
+    const int64_t bytes = numel * elem;
+    const bool small = bytes <= (12 << 20);
+    if (!small && (elem != 4 || info.mode == kAxpby)) return false;
+    const int64_t most = kSharedLdsBudgetAxpby;
+    int64_t budget = std::max<int64_t>(2560, std::min<int64_t>(most, bytes / 200));
+    bool found = false;
+    if (int64_t(t.subRows) * t.pitch * elem <= budget) {
+        found = setup_perm(t, elem, g);
+        g.hints = info.hints == kNtLoad ? 0 : info.hints;
+    }
+    for (; !found; budget = std::min(most, 2 * budget)) {
+        hptt_options_t none;
+        memset(&none, 0, sizeof(none));
+        TileArgs best;
+        hptt_plan_info_t in = info;
+        double score = 0;
+        found = choose_shared(f, elem, none, best, in, score, budget) && setup_perm(best, elem, g);
+        if (found) {
+            set_xcd_groups(none, elem, in, best);
+            g.skew = best.skew;
+            g.xcdGroupLog = best.xcdGroupLog;
+            g.hints = best.alignedB || best.runB * elem >= 2048 ? kNtStore : 0;
+        }
+        if (budget == most) break;
+    }
+    g.use = found && (small || (g.runA >= 256 && g.runB >= 256 && g.numTiles >= 2 * kPermGrid));
+    return g.use != 0;
 }
 
 bool setup_stream(const Fused& f, int elem, const hptt_options_t& opt, StreamArgs& s,
@@ -1617,6 +1733,8 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
     memset(&none, 0, sizeof(none));
     if (k == HPTT_KERNEL_TILE && !sharedTile && memcmp(&opt, &none, sizeof(none)) == 0)
         choose_matrix(f, elem, numel, plan->tile, info, plan->matrix);
+    if (k == HPTT_KERNEL_TILE && sharedTile && memcmp(&opt, &none, sizeof(none)) == 0)
+        choose_perm(f, elem, numel, plan->tile, info, plan->perm);
     return HPTT_SUCCESS;
 }
 
@@ -1646,6 +1764,11 @@ void describe_plan(const hptt_plan_s* p, char* buf, size_t len) {
         snprintf(buf + used, len - used, " matrix=%dx%d of %ux%u shear=%d tiles=%u hints=%d", sh.cols,
                  sh.rows, p->matrix.colsA, p->matrix.rowsB, sh.line, p->matrix.numTiles,
                  p->matrix.hints);
+    }
+    if (p->perm.use && used < len) {
+        const PermArgs& g = p->perm;
+        snprintf(buf + used, len - used, " permute=%dx%d to %dx%d vectors=%d tiles=%u grid=%u lds=%d hints=%d",
+                 g.runA, g.rows, g.runB, g.colsS, g.vectors, g.numTiles, g.grid, g.ldsBytes, g.hints);
     }
 }
 

@@ -11,6 +11,7 @@ struct hptt_plan_s {
     double beta;   // rounded to dtype
     hptt::TileArgs tile;
     hptt::MatrixArgs matrix;  // matrix.use: launched instead of tile
+    hptt::PermArgs perm;      // perm.use: likewise
     hptt::StreamArgs stream;
     hptt::GenericArgs generic;
 };

@@ -19,6 +19,9 @@ const void* tile_kernel_f64(int variant, int mode, int hints, int va, int vb, in
 // Address of kernel M for (shape, update mode, cache hints); tile_matrix.hip.
 const void* matrix_kernel_f32(int shape, int mode, int hints);
 const void* matrix_kernel_f64(int shape, int mode, int hints);
+// Address of kernel P for (vectors per lane, update mode, cache hints); tile_perm.hip.
+const void* perm_kernel_f32(int vectors, int mode, int hints);
+const void* perm_kernel_f64(int vectors, int mode, int hints);
 
 namespace {
 

@@ -23,6 +23,7 @@
 
 #include "kernel_body.h"
 #include "matrix_body.h"
+#include "perm_body.h"
 #include "plan.h"
 
 namespace {
@@ -399,6 +400,50 @@ bool emu_matrix_shape(const hptt_plan_s* p, const T* A, T* B, int64_t blockStrid
     return true;
 }
 
+// Mirrors perm_kernel in tile_perm.hip: a workgroup's tiles one after another.
+template <typename T, int N, int MODE>
+void emu_perm(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
+    using namespace hptt;
+    const PermArgs& g = p->perm;
+    const T alpha = T(p->alpha), beta = T(p->beta);
+    S->lds.assign(size_t(g.ldsBytes), 0);
+    S->written.assign(size_t(g.ldsBytes), 0);
+    T* lds = reinterpret_cast<T*>(S->lds.data());
+    std::vector<PermLane<T, N>> lanes(kBlock);
+    for (int64_t blk = 0; blk < int64_t(g.grid) && S->errors == 0; blk += blockStride) {
+        for (int tid = 0; tid < kBlock; ++tid) perm_setup<T, N>(g, tid, lanes[tid]);
+        for (int64_t t = blk; t < int64_t(g.numTiles) && S->errors == 0; t += g.grid) {
+            clear_written(0, g.ldsBytes);
+            const PermTile tile = perm_tile(g, uint32_t(t));
+            for (int tid = 0; tid < kBlock; ++tid) {
+                Vec<T, PermLane<T, N>::V> x[N];
+                memset(x, 0, sizeof(x));
+                perm_load<HostMem, T, N, 0>(g, tile, tid, lanes[tid], A, x);
+                perm_stage<HostMem, T, N>(g, tid, lanes[tid], lds, x);
+            }
+            for (int tid = 0; tid < kBlock; ++tid) {
+                Vec<T, PermLane<T, N>::V> y[N];
+                memset(y, 0, sizeof(y));
+                if (MODE == kAxpby) perm_prior<HostMem, T, N, 0>(g, tile, tid, lanes[tid], B, y);
+                perm_store<HostMem, T, N, MODE, 0>(g, tile, tid, lanes[tid], B, lds, y, alpha, beta);
+            }
+        }
+    }
+}
+
+template <typename T, int MODE>
+bool emu_perm_vectors(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
+    if (!p->perm.use) return false;
+    switch (p->perm.vectors) {
+        case 1: emu_perm<T, 1, MODE>(p, A, B, blockStride); break;
+        case 2: emu_perm<T, 2, MODE>(p, A, B, blockStride); break;
+        case 3: emu_perm<T, 3, MODE>(p, A, B, blockStride); break;
+        case 5: emu_perm<T, 5, MODE>(p, A, B, blockStride); break;
+        default: fail("vectors per lane", p->perm.vectors, 0);
+    }
+    return true;
+}
+
 // The variant and workgroup size hptt_exec would launch, or a forced variant:
 // kGeneral serves any plan, kShifted and kFast any plan kDirect serves,
 // kShifted any plan kFast serves.
@@ -406,7 +451,9 @@ template <typename T, int VA, int VB, int MODE, int NT>
 void emu_tile(const hptt_plan_s* p, const T* A, T* B, int64_t blockStride) {
     using namespace hptt;
     // a forced variant is one of kernel T's
-    if (S->forceVariant < 0 && emu_matrix_shape<T, MODE>(p, A, B, blockStride)) return;
+    if (S->forceVariant < 0 && (emu_matrix_shape<T, MODE>(p, A, B, blockStride) ||
+                                emu_perm_vectors<T, MODE>(p, A, B, blockStride)))
+        return;
     TileArgs g = p->tile;
     g.misA = int32_t(S->misA % VA);
     g.misB = int32_t(S->misB % VB);
