@@ -958,7 +958,11 @@ int matrix_shape(const Fused& f, int elem, int64_t numel, const hptt_plan_info_t
         return m.cols < 56 || (readsB && m.cols < 112) ? 0 : 1;
     }
     if (m.cols < 12) return m.rows >= 128 ? 2 : 5;
-    if (halfLines) return bytes >= (20 << 20) && m.cols >= 24 ? 3 : 5;
+    if (halfLines) {
+        // (96 columns by 16 rows, 18 MB: 16 us, kernel T 11)
+        if (m.rows <= 16 && bytes >= (8 << 20)) return -1;
+        return bytes >= (20 << 20) && m.cols >= 24 ? 3 : 5;
+    }
     if (m.rows <= 24) return 4;
     if (m.rows < 64 || bytes < (3 << 20)) return 5;
     return m.rows < 256 || bytes < (20 << 20) || m.cols < 24 ? 1 : 0;
@@ -974,6 +978,18 @@ void choose_matrix(const Fused& f, int elem, int64_t numel, const TileArgs& t,
     const MatrixShapeInfo& sh = elem == 4 ? kShapes32[id] : kShapes64[id];
     MatrixGroups m;
     if (!matrix_groups(f, sh.cols, m) || !setup_matrix(f, elem, sh, m, info.grid_order, g)) {
+        g.use = 0;
+        return;
+    }
+    // Tiles that the problem leaves mostly empty: with 2 to 4 columns (or rows)
+    // of 8 or 16, well under half of a tile in use, kernel T is faster from 32 MB
+    // on (fp64 2x9909223 65 us against 79, fp32 4x9322372 60 against 79, 8x130 of
+    // 198 MB 122 against 139; fp64 2 x 2156 x 525, 18 MB, 17 against 14); with less than a tenth it is from 2 MB on
+    // (fp64 2x23x134079 34 against 117, fp32 2 rows of 414720 12 against 20).
+    auto part = [](int64_t n, int64_t of) { return double(n) / double((n + of - 1) / of * of); };
+    const double inUse = part(m.cols, sh.cols) * part(m.rows, sh.rows);
+    const int64_t bytes = numel * elem;
+    if ((inUse < 0.45 && bytes >= (32 << 20)) || (inUse < 0.1 && bytes >= (2 << 20))) {
         g.use = 0;
         return;
     }

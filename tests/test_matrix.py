@@ -100,3 +100,17 @@ def test_gpu(size, perm, dtype, shape):
     dB = torch.from_numpy(B0[:n].copy()).cuda()
     p.exec(dA[:n], dB)
     assert np.array_equal(dB.cpu().numpy(), want), (p.describe(), cut_b)
+
+
+@pytest.mark.parametrize("size,perm,dtype,taken", [
+    ((2, 23, 134079), (1, 0, 2), "f64", False),     # 2 x 23 of 16 x 64
+    ((2, 9909223), (1, 0), "f64", False),           # 2 of 8 columns, 159 MB
+    ((2, 398160), (1, 0), "f64", True),             # the same, 6 MB
+    ((8, 13, 10, 3179, 15), (1, 2, 0, 3, 4), "f32", False),
+    ((8, 12, 17266, 2, 29), (1, 2, 0, 4, 3), "f32", True),   # 8 of 16 columns
+    ((2, 48, 8, 93, 2, 16), (5, 0, 1, 3, 2, 4), "f64", False),
+])
+def test_mostly_empty_tiles(size, perm, dtype, taken):
+    """Tiles that the problem leaves mostly empty are taken where it is small."""
+    from paper_1704_04374_amd import hptt
+    assert ("matrix=" in hptt.create_plan(perm, size, 1.0, 0.0, dtype).describe()) == taken
