@@ -936,11 +936,22 @@ int matrix_shape(const Fused& f, int elem, int64_t numel, const hptt_plan_info_t
     if (elem == 4) {
         // Large fp32 problems whose runs are whole lines on both sides stay
         // with kernel T (variants kDirect and kFast), whose tiles take an
-        // index's own extents as runs: 8192 x 8192 92 us against 96, the 6-D
-        // 24x20x16x24x18x20 99 against 103, 3x2x640x480x96 with beta = 1 353
-        // against 363.  Smaller ones gain with kernel M (4096 x 4096 28 -> 26,
-        // 2048 x 2048 9.4 -> 8.2, 1024 x 1024 6.2 -> 3.7).
-        if (bytes >= (100 << 20) && t.alignedA && t.alignedB && !t.shear && t.nZ == 1) return -1;
+        // index's own extents as runs: 8192 x 8192 92 us against 94 to 97, the
+        // 6-D 24x20x16x24x18x20 94 against 96 to 98, 3x2x640x480x96 with beta = 1
+        // 353 against 371.  Up to 180 MiB 128 x 32 tiles are 1 to 30 % faster on 25
+        // of 26 (5120 x 5632 48 us -> 45.5, 6400 x 6400 with beta = 1 101 -> 98,
+        // 64x352x32x48 73 -> 56), unless the columns leave the last tile partly
+        // empty (96 columns 80 -> 134) or, with B read, lie multiples of 16 KiB apart
+        // in B (2048 x 16384 77 -> 85; 8 KiB, 16384 x 2048, 80 -> 70).  Below 100 MiB
+        // other shapes gain too (4096 x 4096 28 -> 26, 2048 x 2048 9.4 -> 8.2,
+        // 1024 x 1024 6.2 -> 3.7).
+        if (bytes >= (100 << 20) && t.alignedA && t.alignedB && !t.shear && t.nZ == 1) {
+            MatrixGroups w;
+            if (bytes >= (180 << 20) || !lines || !matrix_groups(f, 128, w)) return -1;
+            const bool full = w.cols * 5 >= (w.cols + 127) / 128 * 128 * 4;
+            const bool apart = readsB && (f.sB[0] * elem) % (16 << 10) == 0;
+            return full && !apart ? 4 : -1;
+        }
         // few columns: 16 of them, by 256 rows where there are enough
         if (m.cols < 17) return bytes < (4 << 20) || m.rows < 256 ? 7 : 2;
         // small problems: the most tiles (36x255x22 10.4 us -> 3.5 against

@@ -20,6 +20,7 @@ CASES = [
     ((130, 608, 12), (1, 2, 0), "f32", "64x64"),
     ((800, 224, 6), (1, 0, 2), "f32", "128x32"),
     ((1030, 96, 12), (1, 0, 2), "f32", "32x32"),
+    ((5120, 5632), (1, 0), "f32", "128x32"),             # 100 to 180 MiB
     ((257, 97, 185), (1, 0, 2), "f32", "32x128"),        # short rows off the lines
     ((50, 601, 145), (1, 0, 2), "f32", "32x128"),        # sheared
     ((5, 13, 40, 1700), (3, 2, 1, 0), "f32", "64x64"),
