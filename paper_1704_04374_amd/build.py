@@ -3,7 +3,8 @@
 ``python -m paper_1704_04374_amd.build`` compiles every source under ``csrc/``
 (HIP kernels and the host half of the C ABI) into
 ``paper_1704_04374_amd/libhptt.so``.  Objects go to ``_build/`` at the
-repository root.
+repository root, with the command and the compiler's output of every step
+beside them (``<step>.log``).
 """
 from __future__ import annotations
 
@@ -12,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import time
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -45,42 +47,54 @@ def hipcc() -> str:
     return path
 
 
-def _compile(src: str) -> str:
+def run_step(name: str, cmd: list, verbose: bool = False) -> None:
+    """Run one compiler or linker command and keep its output in
+    ``_build/<name>.log``.  A failure is raised with all that is known of it:
+    the step, its exit status (negative: ended by that signal), how long it
+    ran, the command and the output."""
+    os.makedirs(BUILD, exist_ok=True)
+    start = time.monotonic()
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
+                       errors="replace")
+    took = time.monotonic() - start
+    head = f"{name}: exit status {r.returncode} after {took:.1f} s"
+    with open(os.path.join(BUILD, name + ".log"), "w") as f:
+        f.write(f"{head}\n{' '.join(cmd)}\n{r.stdout}")
+    if verbose:
+        print(head, flush=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"build step {head}\n{' '.join(cmd)}\n{r.stdout}")
+
+
+def _compile(src: str, verbose: bool = False) -> str:
     obj = os.path.join(BUILD, os.path.basename(src) + ".o")
     cmd = [hipcc(), *COMMON, "-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".hip"):
         cmd[1:1] = ["-x", "hip", *HIP_ONLY]
     else:  # host code only: no device pass
         cmd[1:1] = ["-x", "hip", f"--offload-arch={ARCH}", "--offload-host-only"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"compiling {src} failed:\n{' '.join(cmd)}\n{r.stdout}{r.stderr}")
+    run_step(os.path.basename(src), cmd, verbose)
     return obj
 
 
+def _link(objs: list, lib: str, libs: list, verbose: bool) -> None:
+    tmp = lib + ".tmp"
+    run_step(os.path.basename(lib), [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs,
+                                     "-o", tmp, *libs], verbose)
+    os.replace(tmp, lib)
+
+
 def build(verbose: bool = False) -> str:
-    """Compile all sources and link ``libhptt.so``; return its path."""
-    os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        objs = list(ex.map(_compile, SOURCES))
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"linking libhptt.so failed:\n{' '.join(cmd)}\n{r.stdout}{r.stderr}")
-    os.replace(tmp, LIB)
-    with cf.ThreadPoolExecutor(max_workers=len(CONTRACT_SOURCES)) as ex:
-        cobjs = list(ex.map(_compile, CONTRACT_SOURCES))
-    tmp = CONTRACT_LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *cobjs, "-o", tmp, f"-L{PKG}",
-           "-lhptt", "-lrocblas", "-Wl,-rpath,$ORIGIN"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"linking libhptt_contract.so failed:\n{' '.join(cmd)}\n"
-                           f"{r.stdout}{r.stderr}")
-    os.replace(tmp, CONTRACT_LIB)
+    """Compile all sources and link ``libhptt.so`` and the contraction library
+    on top of it; return the former's path."""
+    sources = SOURCES + CONTRACT_SOURCES
+    with cf.ThreadPoolExecutor(max_workers=min(8, len(sources))) as ex:
+        objs = list(ex.map(lambda s: _compile(s, verbose), sources))
+    _link(objs[:len(SOURCES)], LIB, [], verbose)
+    _link(objs[len(SOURCES):], CONTRACT_LIB,
+          [f"-L{PKG}", "-lhptt", "-lrocblas", "-Wl,-rpath,$ORIGIN"], verbose)
     if verbose:
-        print(f"built {LIB} and {CONTRACT_LIB}")
+        print(f"built {LIB} and {CONTRACT_LIB}", flush=True)
     return LIB
 
 

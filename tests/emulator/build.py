@@ -7,8 +7,8 @@ for the host only.  The product library ``libhptt.so`` never contains it.
 from __future__ import annotations
 
 import os
-import shutil
-import subprocess
+
+from paper_1704_04374_amd import build as lib_build
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
@@ -19,29 +19,26 @@ LIB = os.path.join(HERE, "libhptt_emulate.so")
 DIRECT_LIB = os.path.join(HERE, "libdirect_emulate.so")
 
 
-def build() -> str:
+def build(verbose: bool = False) -> str:
     _compile([os.path.join(HERE, "emulate.cpp"), os.path.join(CSRC, "plan.cpp"),
-              os.path.join(CSRC, "api.cpp")], LIB)
-    build_direct()
+              os.path.join(CSRC, "api.cpp")], LIB, verbose)
+    build_direct(verbose)
     return LIB
 
 
-def build_direct() -> str:
+def build_direct(verbose: bool = False) -> str:
     return _compile([os.path.join(HERE, "direct_emulate.cpp"),
-                     os.path.join(CSRC, "contract_direct_plan.cpp")], DIRECT_LIB)
+                     os.path.join(CSRC, "contract_direct_plan.cpp")], DIRECT_LIB, verbose)
 
 
-def _compile(srcs, lib) -> str:
-    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+def _compile(srcs, lib, verbose) -> str:
     tmp = f"{lib}.tmp{os.getpid()}"  # one per process: test workers may build at once
-    cmd = [hipcc, "-x", "hip", "--offload-host-only", "-O2", "-g", "-std=c++17", "-fPIC",
+    cmd = [lib_build.hipcc(), "-x", "hip", "--offload-host-only", "-O2", "-g", "-std=c++17", "-fPIC",
            "-shared", "-ffp-contract=off", "-Wall", f"-I{INCLUDE}", f"-I{CSRC}", *srcs, "-o", tmp]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"building the emulator failed:\n{' '.join(cmd)}\n{r.stdout}{r.stderr}")
+    lib_build.run_step(os.path.basename(lib), cmd, verbose)
     os.replace(tmp, lib)
     return lib
 
 
 if __name__ == "__main__":
-    print(build())
+    print(build(verbose=True))

@@ -627,22 +627,14 @@ void run_va(const hptt_plan_s* p, const T* A, T* B, int va, int vb, int64_t bs) 
     else if constexpr (sizeof(T) == 4) run_vb<T, MODE, NT, 4>(p, A, B, vb, bs);
 }
 
-template <typename T, int MODE>
-void run_hint(const hptt_plan_s* p, const T* A, T* B, int va, int vb, int64_t bs) {
-    switch (p->info.hints) {
-        case 0: run_va<T, MODE, 0>(p, A, B, va, vb, bs); break;
-        case hptt::kNtStore: run_va<T, MODE, hptt::kNtStore>(p, A, B, va, vb, bs); break;
-        case hptt::kNtLoad: run_va<T, MODE, hptt::kNtLoad>(p, A, B, va, vb, bs); break;
-        default: run_va<T, MODE, hptt::kNtStore | hptt::kNtLoad>(p, A, B, va, vb, bs);
-    }
-}
-
+// Cache hints (NT) choose an instruction's policy and nothing that the host
+// could follow, so only the variants without one are built.
 template <typename T>
 void run(const hptt_plan_s* p, const T* A, T* B, int va, int vb, int64_t bs) {
     switch (p->info.mode) {
-        case hptt::kCopy: run_hint<T, hptt::kCopy>(p, A, B, va, vb, bs); break;
-        case hptt::kScale: run_hint<T, hptt::kScale>(p, A, B, va, vb, bs); break;
-        default: run_hint<T, hptt::kAxpby>(p, A, B, va, vb, bs);
+        case hptt::kCopy: run_va<T, hptt::kCopy, 0>(p, A, B, va, vb, bs); break;
+        case hptt::kScale: run_va<T, hptt::kScale, 0>(p, A, B, va, vb, bs); break;
+        default: run_va<T, hptt::kAxpby, 0>(p, A, B, va, vb, bs);
     }
 }
 
