@@ -319,7 +319,8 @@ hptt_status_t hptt_contraction_create(hptt_contraction_t* planOut, hptt_dtype_t 
              (long long)ws);
     p->desc = buf;
     if (c.swap) p->desc += " (as C^T = B^T A^T)";
-    if (p->direct) p->desc += " direct";
+    // "nt": C's stores are non-temporal where C starts on a 128-byte line
+    if (p->direct) p->desc += p->dargs.streamC ? " nt direct" : " direct";
     *planOut = p;
     return HPTT_SUCCESS;
 }

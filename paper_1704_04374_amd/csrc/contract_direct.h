@@ -55,7 +55,7 @@ struct DirectArgs {
     // (s >> shk) & (slice - 1), the direction that is contiguous in P first
     int32_t sh1, sh2, shk;
     int32_t shn, shq;  // the same for Q: column (s >> shn) & (kBN - 1), slice (s >> shq)
-    int32_t streamC;  // C written (and read) non-temporally
+    int32_t streamC;  // C, if it starts on a line, written (and read) non-temporally
     // the grid: column blocks first, then x2, x1, batch
     FastDiv tilesY, tiles2, tiles1;
     uint32_t numTiles;

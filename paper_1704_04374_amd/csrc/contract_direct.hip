@@ -190,19 +190,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
 template <typename T>
 const void* kernel_of(bool beta, bool nt) {
-    if (beta)
-        return nt ? reinterpret_cast<const void*>(&direct_kernel<T, true, true>)
-                  : reinterpret_cast<const void*>(&direct_kernel<T, true, false>);
-    return nt ? reinterpret_cast<const void*>(&direct_kernel<T, false, true>)
-              : reinterpret_cast<const void*>(&direct_kernel<T, false, false>);
+    if constexpr (sizeof(T) == 8)  // (plan_direct: never in fp32)
+        if (nt)
+            return beta ? reinterpret_cast<const void*>(&direct_kernel<T, true, true>)
+                        : reinterpret_cast<const void*>(&direct_kernel<T, false, true>);
+    return beta ? reinterpret_cast<const void*>(&direct_kernel<T, true, false>)
+                : reinterpret_cast<const void*>(&direct_kernel<T, false, false>);
 }
 
 }  // namespace
 
 bool launch_direct(const DirectArgs& g, bool f64, const void* P, const void* Q, void* C,
                    double alpha, double beta, hipStream_t stream, hipError_t* err) {
-    const void* fn = f64 ? kernel_of<double>(beta != 0, g.streamC)
-                         : kernel_of<float>(float(beta) != 0.f, g.streamC);
+    // C off the lines: its runs are not whole lines in memory
+    const bool nt = g.streamC && reinterpret_cast<uintptr_t>(C) % 128 == 0;
+    const void* fn =
+        f64 ? kernel_of<double>(beta != 0, nt) : kernel_of<float>(float(beta) != 0.f, nt);
     DirectArgs args = g;
     float af = float(alpha), bf = float(beta);
     double ad = alpha, bd = beta;

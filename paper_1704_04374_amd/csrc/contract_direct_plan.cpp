@@ -42,6 +42,14 @@ void set_group(ModeGroup& g, const std::string& modes, const std::string& t0,
     g.total = int32_t(total);
 }
 
+// Bytes of C that x1's positions fill from C's first one on: every run of rows
+// in C starts at a multiple of it.
+int64_t run_c(const DirectArgs& g, int elem) {
+    int64_t run = elem;
+    for (int j = 0; j < g.x1.n && int64_t(g.x1.s1[j]) == run; ++j) run *= g.x1.ext[j].d;
+    return run;
+}
+
 }  // namespace
 
 bool plan_direct(const std::string& modesP, const std::string& modesQ, const std::string& modesC,
@@ -138,12 +146,17 @@ bool plan_direct(const std::string& modesP, const std::string& modesQ, const std
     if (tiles >= (int64_t(1) << 32) / kBlock) return false;  // a launch counts threads in 32 bits
     g->numTiles = uint32_t(tiles);
     // Non-temporal stores of C where it will not stay in the 256 MiB last-level
-    // cache anyway (MI355X, fp64, 226 MB: 59 -> 53 us; fp32, 107 MB: 25 -> 35
-    // us), sooner where its 16-element runs are written by distant blocks
-    // (fp32, 127 MB 61 -> 50 us, 134 MB 60 -> 50 us).
+    // cache anyway, sooner where its 16-element runs are written by distant
+    // blocks -- in fp64, whose stores are whole lines where C's runs are
+    // (MI355X, 70 contractions of 64 MiB of C and more: 1.03x on average, 0.90 to
+    // 1.11; abcde = efbad.cf 91.8 -> 87.9 us).  A line written in parts that way
+    // goes to memory in parts: runs off the lines lose up to 4x (fp32
+    // adgihcb = eihgfab.egfchid 127 us, 529 non-temporal), and so does fp32,
+    // whose stores are half lines (0.83 to 1.07x on whole-line runs).
     int64_t bytesC = elem;
     for (char c : C) bytesC *= ext[static_cast<unsigned char>(c)];
-    g->streamC = bytesC >= ((x2.empty() ? 128 : 64) << 20);
+    g->streamC = elem == 8 && run_c(*g, elem) % 128 == 0 &&
+                 bytesC >= ((x2.empty() ? 128 : 64) << 20);
     return true;
 }
 
@@ -176,8 +189,7 @@ double direct_us(const DirectArgs& g, int elem) {
     double in, out;
     tensor_bytes(g, elem, &in, &out);
     // runs of C below 64 bytes write parts of its lines
-    int64_t run = elem;
-    for (int j = 0; j < g.x1.n && g.x1.s1[j] == run; ++j) run *= g.x1.ext[j].d;
+    const int64_t run = run_c(g, elem);
     if (run < 64) out *= run < 16 ? 4 : 64.0 / double(run);
     const int bk = direct_slice(elem);
     const double slices = (g.k.total + bk - 1) / bk;

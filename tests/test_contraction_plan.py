@@ -199,3 +199,17 @@ def test_workload_transpositions_dry_run():
                 t = emu.plan([src.index(m) for m in dst], [ext[m] for m in src], al, be, w.dtype)
                 err, msg, _ = emu.run(t, block_stride=max(1, t.info["grid"] // 101))
                 assert err == 0, (w.name, src, dst, msg)
+
+
+@pytest.mark.parametrize("spec,ext,dtype,nt", [
+    ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f64", True),
+    ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f32", False),   # half-line stores
+    # runs of 14 and of 16 elements
+    ("acb=adb*dc", dict(a=14, b=1200, c=1400, d=4), "f64", False),
+    ("acb=adb*dc", dict(a=16, b=1200, c=1400, d=4), "f64", True),
+    ("adgihcb=eihgfab*egfchid", dict(a=2, b=286, c=5, d=579, e=2, f=9, g=7, h=2, i=2), "f32",
+     False),                                                                    # 127 us, 529 nt
+])
+def test_non_temporal_stores_only_of_whole_lines(spec, ext, dtype, nt):
+    p = _plan(spec, ext, dtype=dtype)
+    assert p.describe().endswith(" nt direct") == nt, p.describe()

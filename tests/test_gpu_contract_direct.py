@@ -67,24 +67,44 @@ def test_block_edges(spec, ext):
             assert (np.abs(got - exact) <= oc.error_bound(mag, p.info["gemm_k"], dtype)).all()
 
 
-def test_large_result_and_overlapping_tensors():
-    """C of 64 MiB and more, written non-temporally; and C on top of A, which
-    the transpositions serve because they copy A first."""
-    ext = dict(m=24, q=24, n=96, k=5, r=152)
-    p, c, a, b = _problem("mnqr=qkmr*kn", ext, "f64", 1.0, 0.0)
-    assert p.describe().endswith("direct")
-    A, B = (torch.rand(int(np.prod([ext[m] for m in s])), dtype=torch.float64, device="cuda")
-            for s in (a, b))
-    C = torch.empty(int(np.prod([ext[m] for m in c])), dtype=torch.float64, device="cuda")
-    assert C.numel() * 8 >= 64 << 20
-    print(f"[direct] {p.describe()}", flush=True)
-    p.exec(A, B, C)
-    t = A.view(ext["r"], ext["m"], ext["k"], ext["q"]).permute(0, 3, 1, 2)   # r q m k
-    want = torch.zeros(ext["r"], ext["q"], ext["n"], ext["m"], dtype=torch.float64, device="cuda")
-    bt = B.view(ext["n"], ext["k"])
+@pytest.mark.parametrize("dtype,m,nt", [("f64", 32, True), ("f64", 24, False), ("f32", 64, False)])
+@pytest.mark.parametrize("beta", [0.0, 1.25])
+def test_large_result(dtype, m, nt, beta):
+    """C of 64 MiB and more: written non-temporally in fp64 where its runs (m
+    elements) are whole lines, in either update mode, and with C on a line and
+    one element off it, where the stores are ordinary ones."""
+    ext = dict(m=m, q=24, n=96, k=5, r=152)
+    p, c, a, b = _problem("mnqr=qkmr*kn", ext, dtype, 0.75, beta)
+    assert p.describe().endswith(" nt direct" if nt else " direct")
+    assert (" nt " in p.describe()) == nt
+    print(f"[direct] {p.describe()} beta={beta}", flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    A, B, C = (torch.rand(int(np.prod([ext[x] for x in s])) + (s == c), dtype=tdt, device="cuda",
+                          generator=g) for s in (a, b, c))
+    nc = C.numel() - 1
+    assert nc * C.element_size() >= 64 << 20 and C.data_ptr() % 128 == 0
+    t = A.double().view(ext["r"], ext["m"], ext["k"], ext["q"]).permute(0, 3, 1, 2)   # r q m k
+    prod = torch.zeros(ext["r"], ext["q"], ext["n"], ext["m"], dtype=torch.float64, device="cuda")
+    bt = B.double().view(ext["n"], ext["k"])
     for k in range(ext["k"]):
-        want += t[:, :, None, :, k] * bt[None, None, :, k, None]
-    assert (C.view_as(want) - want).abs().max() <= (ext["k"] + 2) * 2.0 ** -53 * ext["k"]
+        prod += t[:, :, None, :, k] * bt[None, None, :, k, None]
+    u = 2.0 ** (-24 if dtype == "f32" else -53)
+    for off in (0, 1):
+        got = C.clone() if beta else torch.full_like(C, float("nan"))
+        p.exec(A, B, got[off:off + nc])
+        want = 0.75 * prod.view(-1)
+        if beta:
+            want += beta * C[off:off + nc].double()
+        # |A|, |B|, |C| <= 1: the bound of (k + 2) u (|alpha| sum |A||B| + |beta| |C|)
+        bound = (ext["k"] + 2) * u * (0.75 * ext["k"] + abs(beta))
+        assert (got[off:off + nc].double() - want).abs().max() <= bound, off
+        rest = got[nc:] if off == 0 else got[:1]
+        assert bool((rest == (C[nc:] if off == 0 else C[:1])).all() if beta else rest.isnan().all())
+
+
+def test_overlapping_tensors():
+    """C on top of A, which the transpositions serve because they copy A first."""
     ext = dict(m=16, q=8, n=4, k=4)
     p, c, a, b = _problem("mnq=qkm*kn", ext, "f64", 1.0, 0.0)
     assert p.describe().endswith("direct") and p.info["transpose_a"]
