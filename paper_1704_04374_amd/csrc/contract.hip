@@ -114,7 +114,8 @@ hptt_status_t make_transpose(const std::string& from, const std::string& to, con
 // Whether the direct kernel takes the place of transposition - GEMM -
 // transposition; fills p->dargs.  A plan without transpositions is a plain
 // GEMM and stays one, and so does alpha = 0, for which a GEMM reads neither
-// operand.  Otherwise the estimate of each decides: the direct kernel saves
+// operand.  Otherwise the estimate of each decides, with a margin for what
+// they do not know (see direct_us): the direct kernel saves
 // the transposed operands' and product's round trips (MI355X, fp64: abcde =
 // efbad.cf, 32 contracted elements, 243 -> 78 us; abcd = ebad.ce 127 -> 48;
 // fp32 abcd = dbea.ec, 64 contracted, 246 -> 86), the library GEMM has nearly
@@ -129,8 +130,10 @@ bool use_direct(hptt_contraction_s* p) {
         if (hptt::plan_direct(swap ? p->mb : p->ma, swap ? p->ma : p->mb, p->mc, p->ext, elem,
                               &p->dargs)) {
             p->directSwap = swap;
-            return hptt::direct_us(p->dargs, elem) <
-                   hptt::transposed_us(p->dargs, elem, transposes, in.bytes_transposed);
+            const bool beta =
+                p->dtype == HPTT_FLOAT32 ? float(p->beta) != 0.f : p->beta != 0.0;
+            return hptt::direct_us(p->dargs, elem, beta) <
+                   0.95 * hptt::transposed_us(p->dargs, elem, transposes, in.bytes_transposed);
         }
     return false;
 }

@@ -166,7 +166,7 @@ bool plan_direct(const std::string& modesP, const std::string& modesQ, const std
 
 // Estimated time in microseconds (MI355X) of the kernel on a planned problem,
 // and of `transposes` transpositions of `bytesMoved` bytes in all around a GEMM.
-double direct_us(const DirectArgs& g, int elem);
+double direct_us(const DirectArgs& g, int elem, bool beta);
 double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved);
 
 void record_hip_error(hipError_t err);  // libhptt.so: for hptt_last_hip_error

@@ -2,6 +2,8 @@
 // only, no HIP call.
 #include <string.h>
 
+#include <algorithm>
+
 #include "contract_direct.h"
 
 namespace hptt {
@@ -163,7 +165,7 @@ bool plan_direct(const std::string& modesP, const std::string& modesQ, const std
 namespace {
 
 // Two overlapping costs: the larger, and a part of the smaller.
-double overlap(double a, double b) { return a > b ? a + 0.3 * b : b + 0.3 * a; }
+double overlap(double a, double b, double part) { return a > b ? a + part * b : b + part * a; }
 
 double batches(const DirectArgs& g) {
     double v = 1;
@@ -172,46 +174,72 @@ double batches(const DirectArgs& g) {
 }
 
 // Bytes of P, Q and C.
-void tensor_bytes(const DirectArgs& g, int elem, double* in, double* out) {
+void tensor_bytes(const DirectArgs& g, int elem, double* P, double* Q, double* C) {
     const double m = double(g.x1.total) * double(g.x2.total), n = g.y.total, k = g.k.total;
-    *in = (m * k + n * k) * batches(g) * elem;
-    *out = m * n * batches(g) * elem;
+    *P = m * k * batches(g) * elem;
+    *Q = n * k * batches(g) * elem;
+    *C = m * n * batches(g) * elem;
+}
+
+// How many times over the 64 bytes around an element of an operand are read:
+// a block reads one batch index, so where a batch mode lies within those 64
+// bytes the rest of them is another block's.
+double spread(const DirectArgs& g, const int64_t* strides) {
+    double s = 1;
+    for (int j = 0; j < g.nL; ++j)
+        if (strides[j] < 64) s = std::max(s, 64.0 / double(strides[j]));
+    return s;
 }
 
 }  // namespace
 
-// The constants of both estimates come from 16 benchmark contractions (fp64
-// and fp32) and, for the latencies of small ones, 55 random ones on MI355X
-// (the choice that they make costs 2 % on average against the faster way; a
-// wrong one up to 1.35x, where the direct kernel is left out).
-double direct_us(const DirectArgs& g, int elem) {
+// The constants are fitted to 5,789 random contractions on MI355X (fp64 and
+// fp32, 2,405 of them with batch modes, 1,932 with beta = 1; tensors to 300 MB,
+// most read from memory): the estimate's logarithm is within 0.19 (one standard
+// deviation) of the measured one.  With the margin that use_direct asks for the
+// calls take 0.713 of transposition - GEMM - transposition on average; 46 of
+// them are more than 3 % slower than that, 23 more than 10 %, the worst 1.37x.
+// Without the spread of the batch modes, the read of C and the margin it was
+// 0.712, 131, 91 and up to 4.4x.
+double direct_us(const DirectArgs& g, int elem, bool beta) {
     const bool f64 = elem == 8;
-    double in, out;
-    tensor_bytes(g, elem, &in, &out);
+    double P, Q, C;
+    tensor_bytes(g, elem, &P, &Q, &C);
     // runs of C below 64 bytes write parts of its lines
     const int64_t run = run_c(g, elem);
-    if (run < 64) out *= run < 16 ? 4 : 64.0 / double(run);
+    if (run < 64) C *= run < 16 ? 4 : 64.0 / double(run);
+    if (beta) C *= 2.5;
     const int bk = direct_slice(elem);
     const double slices = (g.k.total + bk - 1) / bk;
     const double rows = double(g.tiles1.d) * g.tiles2.d * kBM;
     const double cols = (g.y.total + 15) / 16 * 16.0;  // products of 16 columns are left out
     const double flops = 2.0 * rows * cols * slices * bk * batches(g);
-    const double stream = overlap(flops / (f64 ? 35e6 : 64e6), (in + out) / 4.2e6);
+    // what is read again: the other parts of lines that hold several batches,
+    // more so in a tensor beyond the L2 caches, and the operands by other blocks
+    const double sP = spread(g, g.sLP), sQ = spread(g, g.sLQ);
+    const double far = 8e6;
+    const double again = (sP - 1) * (0.3 * P + std::max(0.0, P - far)) +
+                         (sQ - 1) * (0.3 * Q + std::max(0.0, Q - far)) +
+                         0.13 * (sP * P * (g.tilesY.d - 1.0) +
+                                 sQ * Q * (double(g.tiles1.d) * g.tiles2.d - 1.0));
+    const double stream = overlap(flops / (f64 ? 78e6 : 140e6), (P + Q + C + again) / 5.8e6, 0.9);
     // a block's slices follow each other; about 1024 blocks run at one time
     const double rounds = (g.numTiles + 1023) / 1024;
-    const double chain = rounds * slices * (f64 ? 1.3 : 1.35);
-    return 5 + overlap(stream, chain);
+    const double chain = rounds * (slices * (f64 ? 1.0 : 1.2) + (beta ? 2.0 : 0.0) + 0.9);
+    return 3.7 + overlap(stream, chain, 0.9);
 }
 
+// (fitted to 16 benchmark contractions and, for the latencies of small ones, 55
+// random ones)
 double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved) {
-    double in, out;
-    tensor_bytes(g, elem, &in, &out);
+    double P, Q, C;
+    tensor_bytes(g, elem, &P, &Q, &C);
     const double flops =
         2.0 * g.x1.total * double(g.x2.total) * g.y.total * double(g.k.total) * batches(g);
     // a long contraction is a chain for the GEMM too
     const double k = g.k.total < 700 ? g.k.total : 700;
     return 7.6 + 2.3 * transposes + bytesMoved / 4.5e6 + k * (elem == 8 ? 0.022 : 0.013) +
-           overlap(flops / (elem == 8 ? 58e6 : 125e6), (in + out) / 4e6);
+           overlap(flops / (elem == 8 ? 58e6 : 125e6), (P + Q + C) / 4e6, 0.3);
 }
 
 }  // namespace hptt

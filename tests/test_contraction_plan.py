@@ -201,6 +201,31 @@ def test_workload_transpositions_dry_run():
                 assert err == 0, (w.name, src, dst, msg)
 
 
+# What the library takes for a call, with what both ways took on an MI355X (us)
+DIRECT_CHOICES = [
+    # an operand that starts with a batch mode: lines that hold several batches
+    ("abd=dca*cbd", dict(a=3536, b=30, c=31, d=144), "f64", 0.0, False),         # 306, 110
+    ("bface=fedab*fdce", dict(a=6, b=710, c=19, d=112, e=11, f=4), "f32", 0.0, False),  # 318, 110
+    ("bcea=eadb*edc", dict(a=10, b=159, c=4, d=280, e=74), "f64", 0.0, False),   # 540, 202
+    ("aihebcd=ifcgbah*hifdge", dict(a=4, b=4, c=4, d=235, e=9, f=2, g=5, h=4, i=57), "f64", 1.0,
+     False),                                                                     # 587, 243
+    ("abc=bda*dc", dict(a=512, b=256, c=256, d=24), "f64", 1.0, False),          # C is read: 179, 138
+    # a batch mode behind whole lines, and few bytes
+    ("bdacge=fcgab*edfg", dict(a=4, b=8, c=14, d=43, e=8, f=7, g=176), "f64", 0.0, True),  # 55, 170
+    ("mnlq=mlkq*knl", dict(m=10, q=13, n=9, k=5, l=3), "f64", 1.25, True),
+    ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f64", 0.0, True),      # 50, 62
+    ("abcde=efbad*cf", dict(a=24, b=24, c=96, d=24, e=24, f=32), "f64", 1.0, True),    # 153, 269
+    ("abcd=dbea*ec", dict(a=96, b=64, c=96, d=64, e=64), "f32", 1.0, True),            # 157, 260
+    ("ab=acd*dbc", dict(a=2048, b=2048, c=64, d=64), "f64", 0.0, False),               # 801, 543
+]
+
+
+@pytest.mark.parametrize("spec,ext,dtype,beta,direct", DIRECT_CHOICES)
+def test_direct_or_transposed(spec, ext, dtype, beta, direct):
+    p = _plan(spec, ext, beta=beta, dtype=dtype)
+    assert p.describe().endswith("direct") == direct, p.describe()
+
+
 @pytest.mark.parametrize("spec,ext,dtype,nt", [
     ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f64", True),
     ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f32", False),   # half-line stores
