@@ -999,8 +999,15 @@ void choose_matrix(const Fused& f, int elem, int64_t numel, const TileArgs& t,
     // (fp64 2x23x134079 34 against 117, fp32 2 rows of 414720 12 against 20).
     auto part = [](int64_t n, int64_t of) { return double(n) / double((n + of - 1) / of * of); };
     const double inUse = part(m.cols, sh.cols) * part(m.rows, sh.rows);
+    // An eighth of a tile or less also from 8 MB on (16 x 8 and 4 x 32 of 16 x 64,
+    // 16 MB: 28 us against 48, 25 against 31), and where kernel T has less
+    // than half as many tiles, from 3500 on (1 to 2 MB blocks of larger tensors with 2 rows
+    // of 64: 5.8 us against 9.6, 8.0 against 12.4; with as many tiles kernel M is
+    // ahead: 11 x 2 of 16 x 64, 11780 tiles each, 0.71 of the time).
     const int64_t bytes = numel * elem;
-    if ((inUse < 0.45 && bytes >= (32 << 20)) || (inUse < 0.1 && bytes >= (2 << 20))) {
+    if ((inUse < 0.45 && bytes >= (32 << 20)) || (inUse < 0.1 && bytes >= (2 << 20)) ||
+        (inUse < 0.13 && (bytes >= (8 << 20) ||
+                          (g.numTiles >= 3500 && g.numTiles / 2 > t.numTiles)))) {
         g.use = 0;
         return;
     }
@@ -1195,6 +1202,13 @@ bool choose_perm(const Fused& f, int elem, int64_t numel, const TileArgs& t,
         }
         if (budget == most) break;
     }
+    // With B read, 3 and 5 vectors per lane hold 59 and 95 registers for one tile
+    // or little more (these sizes have no second one for every workgroup): 5 of
+    // them take 1.12 of kernel T's time from 1 MiB on (16 drawn problems, up to 1.67),
+    // 3 from 6 MiB on 1.03 (25, up to 1.25); the others 0.76 (586).
+    if (found && info.mode == kAxpby &&
+        ((g.vectors == 5 && bytes >= (1 << 20)) || (g.vectors == 3 && bytes >= (6 << 20))))
+        found = false;
     g.use = found && (small || (g.runA >= 256 && g.runB >= 256 && g.numTiles >= 2 * kPermGrid));
     return g.use != 0;
 }

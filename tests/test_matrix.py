@@ -115,3 +115,18 @@ def test_mostly_empty_tiles(size, perm, dtype, taken):
     """Tiles that the problem leaves mostly empty are taken where it is small."""
     from paper_1704_04374_amd import hptt
     assert ("matrix=" in hptt.create_plan(perm, size, 1.0, 0.0, dtype).describe()) == taken
+
+
+@pytest.mark.parametrize("size,perm,outer_a,outer_b,dtype,taken", [
+    ((16, 8, 128, 8, 32), (3, 0, 1, 4, 2), (20, 10, 129, 12, 35), (10, 17, 11, 35, 130), "f32", False),
+    ((141908, 2), (1, 0), (141912, 2), (7, 141911), "f32", False),
+    ((8969, 18, 2), (2, 0, 1), (8970, 21, 2), (4, 8970, 18), "f32", False),
+    ((2, 4, 69, 245), (1, 3, 2, 0), (6, 4, 73, 250), (6, 250, 73, 4), "f64", False),
+    ((8969, 2, 2), (2, 0, 1), (8970, 3, 2), (4, 8970, 2), "f32", True),     # few tiles
+])
+def test_mostly_empty_tiles_of_blocks(size, perm, outer_a, outer_b, dtype, taken):
+    """Blocks of larger tensors, whose two rows (or columns) make a matrix each:
+    taken where they are few."""
+    from paper_1704_04374_amd import hptt
+    p = hptt.create_plan(perm, size, 2.0, 0.5, dtype, outer_size_a=outer_a, outer_size_b=outer_b)
+    assert ("matrix=" in p.describe()) == taken, p.describe()

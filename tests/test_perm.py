@@ -99,3 +99,19 @@ def test_gpu(size, perm, dtype, tile):
     dB = torch.from_numpy(B0[:n].copy()).cuda()
     p.exec(dA[:n], dB)
     assert np.array_equal(dB.cpu().numpy(), want), (p.describe(), cut_b)
+
+
+@pytest.mark.parametrize("size,perm,dtype,beta,taken", [
+    ((5, 6820, 2, 3, 2, 2, 2), (0, 4, 3, 2, 6, 5, 1), "f32", 0.5, False),    # 20 us, kernel T 12
+    ((2, 512, 128, 4), (3, 0, 2, 1), "f64", 0.5, False),
+    ((5, 6820, 2, 3, 2, 2, 2), (0, 4, 3, 2, 6, 5, 1), "f32", 0.0, True),     # B not read
+    ((9, 46, 21, 17), (2, 1, 3, 0), "f32", 0.5, True),                       # below 1 MiB
+    ((304944, 5), (1, 0), "f64", 1.0, False),                                # 3 vectors, 11.6 MiB
+    ((24944, 5), (1, 0), "f64", 1.0, True),
+])
+def test_many_vectors_with_b_read(size, perm, dtype, beta, taken):
+    """Tiles of five vectors per lane are not taken from 1 MiB on where B is read,
+    tiles of three not from 6 MiB on."""
+    from paper_1704_04374_amd import hptt
+    p = hptt.create_plan(perm, size, 1.0, beta, dtype)
+    assert ("permute=" in p.describe()) == taken, p.describe()
