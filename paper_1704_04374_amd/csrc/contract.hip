@@ -100,6 +100,12 @@ struct hptt_contraction_s {
 
 namespace {
 
+// Operands up to half the last-level cache are read by the GEMM from there:
+// written non-temporally they had gone to memory (MI355X, fp64: bgac =
+// efadbg.cdegf 104 us against 89, facb = fdae.cefdb 64 against 51, where kernel
+// T's ordinary stores had made it 92 and 59).
+constexpr int64_t kCachedBytes = int64_t(128) << 20;
+
 hptt_status_t make_transpose(const std::string& from, const std::string& to, const int64_t* ext,
                              double alpha, double beta, hptt_dtype_t dtype, hptt_plan_t* plan) {
     const int n = int(from.size());
@@ -280,6 +286,8 @@ hptt_status_t hptt_contraction_create(hptt_contraction_t* planOut, hptt_dtype_t 
         delete p;
         return st;
     }
+    if (p->planP && volume(P, ext) * elem <= kCachedBytes) hptt::keep_cached(p->planP);
+    if (p->planQ && volume(Q, ext) * elem <= kCachedBytes) hptt::keep_cached(p->planQ);
     p->wsBytes = ws;
     hptt_contraction_info_t& in = p->info;
     memset(&in, 0, sizeof(in));

@@ -15,6 +15,7 @@
 
 #include <string>
 
+#include "hptt.h"
 #include "hptt_args.h"
 
 namespace hptt {
@@ -169,7 +170,10 @@ bool plan_direct(const std::string& modesP, const std::string& modesQ, const std
 double direct_us(const DirectArgs& g, int elem, bool beta);
 double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved);
 
-void record_hip_error(hipError_t err);  // libhptt.so: for hptt_last_hip_error
+// In libhptt.so: a failed launch's error, for hptt_last_hip_error; and a plan
+// whose result is read next, so that nothing of it is stored non-temporally.
+void record_hip_error(hipError_t err);
+void keep_cached(hptt_plan_t plan);
 
 // Queue the kernel; false (and the HIP error) if the launch failed.
 bool launch_direct(const DirectArgs& g, bool f64, const void* P, const void* Q, void* C,

@@ -1779,6 +1779,11 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
     return HPTT_SUCCESS;
 }
 
+void keep_cached(hptt_plan_t plan) {
+    plan->info.hints &= ~kNtStore;
+    plan->matrix.hints = plan->perm.hints = 0;  // (their loads are hinted only with the stores)
+}
+
 void describe_plan(const hptt_plan_s* p, char* buf, size_t len) {
     static const char* kKernel[] = {"auto", "none", "axpby", "stream", "tile", "generic"};
     static const char* kMode[] = {"copy", "scale", "axpby"};

@@ -25,6 +25,9 @@ hptt_status_t build_plan(const int32_t* perm, int32_t N, const int64_t* sizeA,
                          double beta, hptt_dtype_t dtype, const hptt_options_t* options,
                          hptt_plan_s* plan);
 
+// Store nothing of the plan's result non-temporally: it is read next.
+void keep_cached(hptt_plan_t plan);
+
 // Keep a failed launch's error for hptt_last_hip_error (this thread).
 void record_hip_error(hipError_t err);
 

@@ -238,3 +238,23 @@ def test_direct_or_transposed(spec, ext, dtype, beta, direct):
 def test_non_temporal_stores_only_of_whole_lines(spec, ext, dtype, nt):
     p = _plan(spec, ext, dtype=dtype)
     assert p.describe().endswith(" nt direct") == nt, p.describe()
+
+
+@pytest.mark.parametrize("size,perm,dtype,part", [
+    ((130, 608, 12), (1, 2, 0), "f32", "matrix="),
+    ((3, 21, 31, 3, 2, 17), (1, 3, 5, 2, 0, 4), "f32", "permute="),
+    ((64, 9, 40), (0, 2, 1), "f64", "kernel=stream"),
+    ((8192, 8192), (1, 0), "f32", "kernel=tile"),
+])
+def test_operands_are_not_stored_non_temporally(size, perm, dtype, part):
+    """What contractions do to the plans of operands that the GEMM reads next:
+    no store hint is left, whichever kernel the plan takes."""
+    import re
+    p = hptt.create_plan(perm, size, 1.0, 0.0, dtype)
+    assert part in p.describe(), p.describe()
+    hints = [int(h) for h in re.findall(r"hints=(\d)", p.describe())]
+    keep = p._lib._ZN4hptt11keep_cachedEP11hptt_plan_s
+    keep.argtypes, keep.restype = [type(p.handle)], None
+    keep(p.handle)
+    kept = [int(h) for h in re.findall(r"hints=(\d)", p.describe())]
+    assert any(h & 1 for h in hints) and not any(h & 1 for h in kept), (hints, kept)
