@@ -137,9 +137,10 @@ struct DeviceMem {
     __device__ __forceinline__ static T lds_ld(const T* l, int64_t i) {
         return l[i];
     }
-    // A word that may not have been written; the caller then drops it.
+    // A word that may not have been written unless it is kept (for the host's
+    // checks); the caller drops the others.
     template <typename T>
-    __device__ __forceinline__ static T lds_any(const T* l, int64_t i) {
+    __device__ __forceinline__ static T lds_any(const T* l, int64_t i, bool /*kept*/) {
         return l[i];
     }
     template <typename T>

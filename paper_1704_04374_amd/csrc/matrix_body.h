@@ -168,7 +168,10 @@ __host__ __device__ inline void matrix_store_part(const MatrixArgs& g, const Mat
             lo[u] = m.row0 + s - d;
 #pragma unroll
             for (int e = 0; e < V; ++e)
-                x[u].v[e] = Mem::template lds_any<T>(lds, at + l + e * SH::pitch);
+                x[u].v[e] = Mem::template lds_any<T>(
+                    lds, at + l + e * SH::pitch,
+                    q >= m.qLo && q < m.qHi &&
+                        (!EDGE || (lo[u] + e >= 0 && lo[u] + e < int(g.rowsB))));
             if (MODE == kAxpby && q >= m.qLo && q < m.qHi) {
                 if (!EDGE || (lo[u] >= 0 && lo[u] + V <= int(g.rowsB))) {
                     y[u] = SH::S ? Mem::template ldb<T, V, (HINT & kNtStore) != 0>(base, off[u])

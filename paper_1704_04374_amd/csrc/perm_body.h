@@ -192,7 +192,8 @@ __host__ __device__ inline void perm_store(const PermArgs& g, const PermTile& p,
 #pragma unroll
         for (int e = 0; e < V; ++e) {
             const uint32_t two = l.src[u][e / 2];
-            const T x = Mem::template lds_any<T>(lds, int(e % 2 ? two >> 16 : two & 0xffff));
+            const T x = Mem::template lds_any<T>(lds, int(e % 2 ? two >> 16 : two & 0xffff),
+                                                 e < perm_count<V>(p, l.qb[u]));
             z.v[e] = update<MODE>(x, MODE == kAxpby ? y[u].v[e] : T(0), alpha, beta);
         }
         const int n = perm_count<V>(p, l.qb[u]);

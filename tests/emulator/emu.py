@@ -26,6 +26,10 @@ def library():
                                           ctypes.c_int64, ctypes.c_char_p, ctypes.c_size_t,
                                           ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
         lib.hptt_emulate_exec.restype = ctypes.c_int64
+        lib.hptt_emulate_set_shape.argtypes = [ctypes.c_void_p, ctypes.c_int32,
+                                               ctypes.POINTER(ctypes.c_int32),
+                                               ctypes.POINTER(ctypes.c_int32)]
+        lib.hptt_emulate_set_shape.restype = ctypes.c_int32
         lib.hptt_emulate_check_fastdiv.argtypes = [ctypes.c_uint32, ctypes.c_uint64, ctypes.c_uint64]
         lib.hptt_emulate_check_fastdiv.restype = ctypes.c_int64
         _lib = lib
@@ -35,6 +39,14 @@ def library():
 def plan(perm, size_a, alpha=1.0, beta=0.0, dtype="f32", **knobs):
     from paper_1704_04374_amd.hptt import Plan
     return Plan(perm, size_a, alpha, beta, dtype, lib=library(), **knobs)
+
+
+def set_shape(p, shape):
+    """Give a plan of kernel M tile shape number `shape`; its columns and rows."""
+    cols, rows = ctypes.c_int32(), ctypes.c_int32()
+    rc = library().hptt_emulate_set_shape(p.handle, shape, ctypes.byref(cols), ctypes.byref(rows))
+    assert rc == 0, (p.describe(), shape)
+    return cols.value, rows.value
 
 
 VARIANTS = {"fast": 0, "shifted": 1, "general": 2}

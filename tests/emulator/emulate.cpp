@@ -225,7 +225,8 @@ struct HostMem {
         for (int e = 0; e < V; ++e) st1<NT, T>(plus(p, off), e, v.v[e]);
     }
     template <typename T>
-    static T lds_any(const T* l, int64_t i) {
+    static T lds_any(const T* l, int64_t i, bool kept) {
+        if (kept) return lds_ld(l, i);
         const int64_t at = reinterpret_cast<const uint8_t*>(l + i) - S->lds.data();
         if (at < 0 || at + int64_t(sizeof(T)) > int64_t(S->lds.size())) {
             fail("LDS access out of bounds", at, sizeof(T));
@@ -650,7 +651,8 @@ extern "C" {
 // for alignment relative to that grid).  variant >= 0 runs the tile kernel
 // in that variant (kGeneral on any plan, kShifted on plans kFast or kDirect
 // serves, kFast on plans kDirect serves; plans whose runs share indices
-// always run kShared) instead of the one hptt_exec would launch.
+// always run kShared; any other number: the plan's own variant) instead of the
+// kernel hptt_exec would launch.
 // counts (numel
 // bytes, or NULL) is incremented at every B element written.  Only
 // workgroups 0, block_stride, 2*block_stride, ... are run.  Returns the
@@ -684,6 +686,35 @@ int64_t hptt_emulate_exec(hptt_plan_t plan, const void* A, void* B, int32_t va, 
     if (msg && msglen) snprintf(msg, msglen, "%s", st.msg);
     S = nullptr;
     return st.errors;
+}
+
+// Give a plan of kernel M another of its tile shapes (matrix_body.h) and check
+// that it is one.  The columns stay the plan's: a shape with more is partly
+// empty.  0, or -1 if the plan is not kernel M's or the shape does not exist.
+int32_t hptt_emulate_set_shape(hptt_plan_t plan, int32_t shape, int32_t* cols, int32_t* rows) {
+    using namespace hptt;
+    if (!plan || !plan->matrix.use) return -1;
+    struct Shape {
+        int id, cols, rows, line;
+    };
+#define X(id, tc, tr, line) {id, tc, tr, line},
+    const std::vector<Shape> all = plan->dtype == HPTT_FLOAT32
+                                       ? std::vector<Shape>{HPTT_MATRIX_SHAPES_F32(X)}
+                                       : std::vector<Shape>{HPTT_MATRIX_SHAPES_F64(X)};
+#undef X
+    if (shape < 0 || shape >= int(all.size()) || all[size_t(shape)].id != shape) return -1;
+    const Shape& sh = all[size_t(shape)];
+    MatrixArgs& g = plan->matrix;
+    const int64_t rest = sh.line ? sh.line / plan->info.elem_bytes - 1 : 0;
+    const uint32_t others = g.numTiles / (g.chunksC.d * g.chunksR.d);
+    g.shape = shape;
+    g.shear = sh.line > 0;
+    g.chunksC = make_fastdiv(uint32_t((g.colsA + sh.cols - 1) / sh.cols));
+    g.chunksR = make_fastdiv(uint32_t((int64_t(g.rowsB) + rest + sh.rows - 1) / sh.rows));
+    g.numTiles = others * g.chunksC.d * g.chunksR.d;
+    *cols = sh.cols;
+    *rows = sh.rows;
+    return 0;
 }
 
 // Exhaustive check of the fast division used by every kernel: n / d for the

@@ -69,6 +69,43 @@ def test_emulated(size, perm, dtype, shape):
             assert (cnt == 1).all() and np.array_equal(B, want), p.describe()
 
 
+@pytest.mark.parametrize("dtype,shape", [("f32", i) for i in range(8)] + [("f64", i) for i in range(6)])
+def test_every_shape_emulated(dtype, shape):
+    """Each tile shape on small problems with their data, one off its edges in
+    columns and rows, fewer columns and rows than a tile, batches, a sub-block:
+    whatever the plan would choose at that size."""
+    from emulator import emu
+    rng = np.random.default_rng(shape)
+    cols, rows = emu.set_shape(emu.plan((1, 0, 2), (40, 40, 3), 1.0, 0.0, dtype), shape)
+    for c, r, batch in [(cols, rows, 2), (cols + 1, rows - 1, 2), (2 * cols - 1, 2 * rows + 1, 1),
+                        (max(5, cols // 2), rows + 33, 3), (cols + 3, max(3, rows // 3), 3),
+                        (2 * cols, rows + 31, 1)]:
+        for perm, size in (((1, 0, 2), (c, r, batch)), ((1, 2, 0), (c, r, batch))):
+            for alpha, beta in MODES:
+                p = emu.plan(perm, size, alpha, beta, dtype)
+                if "matrix=" not in p.describe():
+                    continue
+                emu.set_shape(p, shape)
+                A, B0 = _rand(rng, p.numel, dtype), _rand(rng, p.numel, dtype)
+                want = orc.transpose(A, size, perm, alpha, beta, B0 if beta != 0 else None)
+                for mis in (0, 1, 3):
+                    B = B0.copy()
+                    err, msg, cnt = emu.run(p, A, B, counts=True, mis_b=mis)
+                    assert err == 0, f"{size} {perm}: {msg}"
+                    assert (cnt == 1).all() and np.array_equal(B, want), (size, perm, mis)
+    # a block of larger tensors: the rest of B is not written
+    size, outer_a, outer_b = (cols + 2, rows + 3, 2), (cols + 5, rows + 4, 2), (rows + 7, cols + 2, 3)
+    p = emu.plan((1, 0, 2), size, 1.5, 0.5, dtype, outer_size_a=outer_a, outer_size_b=outer_b)
+    assert "matrix=" in p.describe(), p.describe()
+    emu.set_shape(p, shape)
+    A, B0 = _rand(rng, int(np.prod(outer_a)), dtype), _rand(rng, int(np.prod(outer_b)), dtype)
+    want = orc.transpose_outer(A, size, (1, 0, 2), outer_a, outer_b, 1.5, 0.5, B0)
+    B = B0.copy()
+    err, msg, _ = emu.run(p, A, B)
+    assert err == 0, msg
+    assert np.array_equal(B, want)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("size,perm,dtype,shape", CASES, ids=_ids)
 def test_gpu(size, perm, dtype, shape):
@@ -97,6 +134,8 @@ def test_gpu(size, perm, dtype, shape):
     cut_b = [cut[q] for q in perm]
     p = hptt.create_plan(perm, cut, 1.5, 0.5, dtype, outer_size_a=size, outer_size_b=size_b)
     print(f"[matrix] {p.describe()}", flush=True)
+    # (too few elements in runs of their own, and a large whole-line problem)
+    assert ("matrix=" in p.describe()) == (size not in ((19, 3, 5, 13), (5120, 5632)))
     want = orc.transpose_outer(A[:n], cut, perm, size, size_b, 1.5, 0.5, B0[:n])
     dB = torch.from_numpy(B0[:n].copy()).cuda()
     p.exec(dA[:n], dB)

@@ -34,6 +34,13 @@ CASES = [
     ((24, 2, 13, 45), (3, 2, 0, 1), "f64", "48x45 to 45x48 vectors=5 tiles=13 "),
     ((24, 26, 26), (2, 0, 1), "f64", "63x26 to 1638x1 vectors=5 tiles=10 "),
 ]
+# the cases whose problem, its last index cut short, is kernel P's too
+CUT_TAKEN = [
+    ((4, 3, 6), "f32"), ((3, 21, 31, 3, 2, 17), "f32"), ((9, 34, 2, 23, 2, 7), "f32"),
+    ((6, 3, 5, 20), "f32"), ((18, 54, 2, 11, 6), "f32"), ((14, 2, 2, 5, 10), "f32"),
+    ((7, 44, 15), "f32"), ((9, 46, 21, 17), "f32"), ((3, 21, 31, 3, 2, 17), "f64"),
+    ((6, 2, 7, 38, 40), "f64"),
+]
 MODES = [(1.0, 0.0), (-0.3, 1.25)]
 
 
@@ -95,6 +102,7 @@ def test_gpu(size, perm, dtype, tile):
     cut_b = [cut[q] for q in perm]
     p = hptt.create_plan(perm, cut, 1.5, 0.5, dtype, outer_size_a=size, outer_size_b=size_b)
     print(f"[permute] {p.describe()}", flush=True)
+    assert ("permute=" in p.describe()) == ((size, dtype) in CUT_TAKEN)
     want = orc.transpose_outer(A[:n], cut, perm, size, size_b, 1.5, 0.5, B0[:n])
     dB = torch.from_numpy(B0[:n].copy()).cuda()
     p.exec(dA[:n], dB)
