@@ -49,7 +49,8 @@ def set_shape(p, shape):
     return cols.value, rows.value
 
 
-VARIANTS = {"fast": 0, "shifted": 1, "general": 2}
+# "tile": kernel T as its plan describes it, also where kernel M or P is launched
+VARIANTS = {"fast": 0, "shifted": 1, "general": 2, "tile": 99}
 
 
 def run(p, A=None, B=None, va=0, vb=0, counts=False, block_stride=1, mis_a=0, mis_b=0,
@@ -58,7 +59,27 @@ def run(p, A=None, B=None, va=0, vb=0, counts=False, block_stride=1, mis_a=0, mi
     of the base pointers from the 16-byte grid (tile kernel); variant:
     "general" (any plan) or "shifted" (plans the fast variant serves) runs the
     tile kernel in that variant instead of the one hptt_exec would launch.
+    Where kernel M or P is launched, the kernel T plan beside it (what the
+    same problem takes with any option) is run as well and has to do the same.
     Returns (errors, msg, counts)."""
+    args = (va, vb, counts, block_stride, mis_a, mis_b)
+    if variant is not None or not any(k in p.describe() for k in (" matrix=", " permute=")):
+        return _run(p, A, B, *args, variant)
+    prior = None if B is None else B.copy()
+    err, msg, cnt = _run(p, A, B, *args, None)
+    if err:
+        return err, msg, cnt
+    err, msg, cnt_t = _run(p, A, prior, *args, "tile")
+    if err:
+        return err, f"kernel T: {msg}", cnt_t
+    if counts and block_stride == 1 and not np.array_equal(cnt, cnt_t):
+        return 1, "kernel T writes other elements of B", cnt_t
+    if B is not None and block_stride == 1 and not np.array_equal(B, prior, equal_nan=True):
+        return 1, "kernel T writes other values to B", cnt_t
+    return 0, "", cnt
+
+
+def _run(p, A, B, va, vb, counts, block_stride, mis_a, mis_b, variant):
     lib = library()
     cnt = np.zeros(p.info["footprint_b"], dtype=np.uint8) if counts else None
     msg = ctypes.create_string_buffer(512)
