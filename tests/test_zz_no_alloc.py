@@ -60,15 +60,27 @@ def _run_pair(p, a, b, c, dtype):
 
 
 def test_no_alloc_matches_exec_twice_second_smaller():
-    # every operand and the product transposed (A, B and C all go through the array)
-    p1, a1, b1, c1 = _case("acbd=aebf*dfce", dict(a=40, b=36, c=44, d=32, e=3, f=5),
+    # every operand and the product transposed (A, B and C all go through the
+    # array): C starts with a batch mode, which the direct kernel refuses
+    p1, a1, b1, c1 = _case("lacbd=aeblf*dflce", dict(a=40, b=18, c=22, d=32, e=3, f=5, l=4),
                            0.75, 1.25, "f64", 1)
-    assert all(p1.info[k] for k in ("transpose_a", "transpose_b", "transpose_c"))
-    _run_pair(p1, a1, b1, c1, "f64")
     # a smaller problem next: the array keeps the first call's larger contents
-    p2, a2, b2, c2 = _case("abc=bda*dc", dict(a=33, b=17, c=29, d=6), -1.5, 0.5, "f32", 2)
+    p2, a2, b2, c2 = _case("lacb=ebla*cle", dict(a=33, b=9, c=29, e=6, l=3), -1.5, 0.5, "f32", 2)
+    for p in (p1, p2):
+        assert all(p.info[k] for k in ("transpose_a", "transpose_b", "transpose_c"))
+        assert not p.describe().endswith("direct")
     assert p2.info["workspace_bytes"] < p1.info["workspace_bytes"]
+    _run_pair(p1, a1, b1, c1, "f64")
     _run_pair(p2, a2, b2, c2, "f32")
+
+
+def test_no_alloc_direct():
+    """Plans that the direct kernel serves leave the array alone."""
+    for spec, ext, dtype in (("acbd=aebf*dfce", dict(a=40, b=36, c=44, d=32, e=3, f=5), "f64"),
+                             ("abc=bda*dc", dict(a=33, b=17, c=29, d=6), "f32")):
+        p, a, b, c = _case(spec, ext, -1.5, 0.5, dtype, 3)
+        assert p.describe().endswith("direct")
+        _run_pair(p, a, b, c, dtype)
 
 
 def test_no_alloc_refuses_plans_beyond_the_array():
