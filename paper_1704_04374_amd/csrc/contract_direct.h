@@ -128,6 +128,30 @@ __host__ __device__ __forceinline__ void direct_column(const DirectArgs& g, cons
     if (d.y + c < g.y.total) group_offsets(g.y, uint32_t(d.y + c), inQ, inC);
 }
 
+// Offsets of slice kb's position j; beyond the contraction those of its first
+// element, whose products are left out.
+__host__ __device__ __forceinline__ void direct_position(const DirectArgs& g, int slice, int kb,
+                                                         int j, uint32_t& inP, uint32_t& inQ) {
+    inP = inQ = 0;
+    if (kb * slice + j < g.k.total) group_offsets(g.k, uint32_t(kb * slice + j), inP, inQ);
+}
+
+// A block's tables, one entry per thread: rows, columns, and slice 0 (which
+// is table 0 of two: slice kb + 1 goes to table (kb + 1) & 1 while the waves
+// are still to multiply slice kb, whose offsets have all been used by then).
+template <int SLICE>
+__host__ __device__ __forceinline__ void direct_tables(const DirectArgs& g, const DirectTile& d,
+                                                       int tid, uint32_t* rowP, uint32_t* rowC,
+                                                       uint32_t* colQ, uint32_t* colC,
+                                                       uint32_t* kP, uint32_t* kQ) {
+    static_assert(kBM + kBN + SLICE <= kBlock, "every entry has a thread");
+    static_assert(kBM == 32 * (kBlock / 64) && kBN == 64, "wave w takes rows 32 w to 32 w + 31");
+    if (tid < kBM) direct_row(g, d, tid, rowP[tid], rowC[tid]);
+    else if (tid < kBM + kBN) direct_column(g, d, tid - kBM, colQ[tid - kBM], colC[tid - kBM]);
+    else if (tid < kBM + kBN + SLICE)
+        direct_position(g, SLICE, 0, tid - kBM - kBN, kP[tid - kBM - kBN], kQ[tid - kBM - kBN]);
+}
+
 // Staging slot s of P: row, slice position and place in a slice's LDS row.
 // Each step of x2 is padded by one element, so that lanes that walk x2
 // write different banks.

@@ -71,15 +71,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const T* P = reinterpret_cast<const T*>(reinterpret_cast<const char*>(P0) + d.offP);
     const T* Q = reinterpret_cast<const T*>(reinterpret_cast<const char*>(Q0) + d.offQ);
     T* C = reinterpret_cast<T*>(reinterpret_cast<char*>(C0) + d.offC);
-    auto slice = [&](int kb, int which, int j) {
-        uint32_t p = 0, q = 0;
-        if (kb * kBK + j < g.k.total) group_offsets(g.k, uint32_t(kb * kBK + j), p, q);
-        kP[which][j] = p;
-        kQ[which][j] = q;
-    };
-    if (tid < kBM) direct_row(g, d, tid, rowP[tid], rowC[tid]);
-    else if (tid < kBM + kBN) direct_column(g, d, tid - kBM, colQ[tid - kBM], colC[tid - kBM]);
-    else if (tid < kBM + kBN + kBK) slice(0, 0, tid - kBM - kBN);
+    direct_tables<kBK>(g, d, tid, rowP, rowC, colQ, colC, kP[0], kQ[0]);
     __syncthreads();
     // this thread's staging slots: offset of the row or column, place in LDS
     // and position in the slice (two 16-bit numbers)
@@ -134,7 +126,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
         for (int u = 0; u < kSlotsQ; ++u) ldsQ[toQ[u] & 0xffff] = vq[u];
         const bool more = kb + 1 < slices;
-        if (more && tid < kBK) slice(kb + 1, (kb + 1) & 1, tid);
+        const int next = (kb + 1) & 1;
+        if (more && tid < kBK) direct_position(g, kBK, kb + 1, tid, kP[next][tid], kQ[next][tid]);
         __syncthreads();
         if (more) fetch(kb + 1);
 #pragma unroll

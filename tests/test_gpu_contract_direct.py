@@ -22,6 +22,7 @@ CASES = [
     ("mnq=mkq*kn", dict(m=64, q=2, n=64, k=16)),
     ("mnq=mkq*kn", dict(m=43, q=3, n=65, k=17)),
     ("mnq=mkq*kn", dict(m=1, q=129, n=1, k=1)),
+    ("mnq=mkq*kn", dict(m=43, q=3, n=63, k=37)),    # a third slice in fp32, a fifth in fp64
     # A leads with a contracted mode, B with a column
     ("mnq=kmq*nk", dict(m=33, q=5, n=70, k=9)),
     # A leads with another row mode than C: 8, 3 x 5 and 9 positions staged side by side
