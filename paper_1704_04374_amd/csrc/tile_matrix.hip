@@ -37,12 +37,14 @@ __global__ __launch_bounds__(kBlock) void matrix_kernel(const T* __restrict__ A,
 
 template <typename T, int MODE, class SH>
 const void* by_hint(int hints) {
-    switch (hints) {
-        case kNtStore | kNtLoad:
+    // non-temporal loads only where a tile's rows are whole lines and start on
+    // them (choose_matrix), which sheared and narrower tiles never have
+    if constexpr (SH::S == 0 && SH::TC * sizeof(T) % 128 == 0)
+        if (hints == (kNtStore | kNtLoad))
             return reinterpret_cast<const void*>(&matrix_kernel<T, MODE, kNtStore | kNtLoad, SH>);
-        case kNtStore: return reinterpret_cast<const void*>(&matrix_kernel<T, MODE, kNtStore, SH>);
-        default: return reinterpret_cast<const void*>(&matrix_kernel<T, MODE, 0, SH>);
-    }
+    return hints == kNtStore ? reinterpret_cast<const void*>(&matrix_kernel<T, MODE, kNtStore, SH>)
+           : hints == 0      ? reinterpret_cast<const void*>(&matrix_kernel<T, MODE, 0, SH>)
+                             : nullptr;
 }
 
 template <typename T, class SH>

@@ -169,3 +169,27 @@ def test_mostly_empty_tiles_of_blocks(size, perm, outer_a, outer_b, dtype, taken
     from paper_1704_04374_amd import hptt
     p = hptt.create_plan(perm, size, 2.0, 0.5, dtype, outer_size_a=outer_a, outer_size_b=outer_b)
     assert ("matrix=" in p.describe()) == taken, p.describe()
+
+
+def test_hints_of_every_plan_have_a_kernel():
+    """Only whole-line tiles of whole-line rows load non-temporally, sheared and
+    narrow ones never: the kernels with that hint that are not built."""
+    import re
+
+    from paper_1704_04374_amd import hptt
+    from paper_1704_04374_amd.workloads import random_problem
+    rng = np.random.default_rng(3)
+    seen = set()
+    for it in range(1500):
+        size, perm = random_problem(rng, max_dims=4, max_numel=1 << 26,
+                                    extents=(2, 7, 16, 32, 64, 96, 100, 128, 512, 513, 2048))
+        dtype = ("f32", "f64")[it % 2]
+        m = re.search(r"matrix=(\d+)x\d+ of .* shear=(\d+) tiles=\d+ hints=(\d)",
+                      hptt.create_plan(perm, size, 1.0, 0.0, dtype).describe())
+        if not m:
+            continue
+        cols, shear, hints = map(int, m.groups())
+        assert hints in (0, 1, 3)
+        assert hints != 3 or (shear == 0 and cols * (4 if dtype == "f32" else 8) % 128 == 0)
+        seen.add(hints)
+    assert seen == {0, 1, 3}
