@@ -121,8 +121,8 @@ typedef struct {
                               one flat range of whole vectors, A read from any
                               element boundary: 0 = where the row walk would move
                               one element per access (odd row lengths), or two
-                              fp32 elements when beta != 0, 1 = wherever B is
-                              compact, 2 = never */
+                              fp32 elements, 1 = wherever B is compact, 2 =
+                              never */
     int32_t grid_order;    /* TILE: order of the grid digits of the indices outside
                               the tile (after the chunk counters): 1 = A order, 2 =
                               by the sum of their strides in A and B, 3 = B
@@ -148,8 +148,11 @@ typedef struct {
 /* What the plan builder decided; for inspection and tests.  Where
  * hptt_describe_plan's line ends in "matrix=...", hptt_exec runs the
  * problem with flattened two-dimensional tiles of that size instead of the
- * TILE plan described here, which hptt_create_plan_ex's options still give;
- * "permute=..." likewise, with shared-run tiles that stay in one workgroup. */
+ * TILE plan described here, which any option other than its default
+ * (hptt_create_plan_ex) still gives; "permute=..." likewise, with shared-run
+ * tiles that stay in one workgroup.  What is launched then stands after that
+ * word in the line; the fields below, tiles, grid, lds_bytes, hints, tile_order
+ * and xcd_group among them, are the TILE plan's. */
 typedef struct {
     int32_t ndim;                      /* rank after dropping extent-1 indices and fusing */
     int64_t size[HPTT_MAX_DIMS];       /* fused extents of A */

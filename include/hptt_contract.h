@@ -42,6 +42,9 @@ extern "C" {
 
 typedef struct hptt_contraction_s *hptt_contraction_t;
 
+/* The arrangement as transpositions and a GEMM.  Plans whose description ends in
+ * "direct" run none of them, except for calls whose C overlaps A or B or whose
+ * tensors are not aligned to their elements. */
 typedef struct {
     int32_t transpose_a;      /* 1: A is transposed into the workspace first */
     int32_t transpose_b;      /* 1: B is transposed into the workspace first */
