@@ -121,11 +121,12 @@ hptt_status_t make_transpose(const std::string& from, const std::string& to, con
 // transposition; fills p->dargs.  A plan without transpositions is a plain
 // GEMM and stays one, and so does alpha = 0, for which a GEMM reads neither
 // operand.  Otherwise the estimate of each decides, with a margin for what
-// they do not know (see direct_us): the direct kernel saves
-// the transposed operands' and product's round trips (MI355X, fp64: abcde =
-// efbad.cf, 32 contracted elements, 243 -> 78 us; abcd = ebad.ce 127 -> 48;
-// fp32 abcd = dbea.ec, 64 contracted, 246 -> 86), the library GEMM has nearly
-// twice its arithmetic rate (ab = acd.dbc, 4096 contracted: 594 us against 841).
+// they do not know (see direct_us): the direct kernel saves the transposed
+// operands' and product's round trips (MI355X, calls in turn on several sets of
+// tensors, fp64: abcde = efbad.cf, 32 contracted elements, 234 -> 88 us; abcd =
+// ebad.ce 117 -> 55; fp32 abcd = dbea.ec, 64 contracted, 237 -> 106), the library
+// GEMM has nearly twice its arithmetic rate (ab = acd.dbc, 4096 contracted: 543
+// us against 801).
 bool use_direct(hptt_contraction_s* p) {
     const bool zero = p->dtype == HPTT_FLOAT32 ? float(p->alpha) == 0.f : p->alpha == 0.0;
     const hptt_contraction_info_t& in = p->info;

@@ -942,7 +942,9 @@ int matrix_shape(const Fused& f, int elem, int64_t numel, const hptt_plan_info_t
         // of 26 (5120 x 5632 48 us -> 45.5, 6400 x 6400 with beta = 1 101 -> 98,
         // 64x352x32x48 73 -> 56), unless the columns leave the last tile partly
         // empty (96 columns 80 -> 134) or, with B read, lie multiples of 16 KiB apart
-        // in B (2048 x 16384 77 -> 85; 8 KiB, 16384 x 2048, 80 -> 70).  Below 100 MiB
+        // in B (2048 x 16384 77 -> 85; 8 KiB, 16384 x 2048, 80 -> 70).  Both ends of
+        // this window and the two spacings are where the sign changed in these
+        // timings; why it changes there is not known.  Below 100 MiB
         // other shapes gain too (4096 x 4096 28 -> 26, 2048 x 2048 9.4 -> 8.2,
         // 1024 x 1024 6.2 -> 3.7).
         if (bytes >= (100 << 20) && t.alignedA && t.alignedB && !t.shear && t.nZ == 1) {
@@ -1033,9 +1035,9 @@ void choose_matrix(const Fused& f, int elem, int64_t numel, const TileArgs& t,
 // Kernel P for the shared-run tiles of t.  False where its packed numbers
 // (16 bits), 32-bit offsets or register vectors do not hold them.
 const int kPermVectors[] = {1, 2, 3, 5};
-// Four workgroups per CU: as many as 95 VGPRs (5 vectors per lane) and 20 KB of
-// LDS leave room for.  With fewer vectors more would fit and were slower
-// (fp32 2925x1207x2x7, perm 2,0,3,1: 86 us with three per CU, 96 with seven).
+// Four workgroups per CU: as many as the 98 VGPRs of 5 vectors per lane leave
+// room for.  With fewer vectors more would fit and were slower (fp32
+// 2925x1207x2x7, perm 2,0,3,1: 86 us with three per CU, 96 with seven).
 constexpr int64_t kPermGrid = 1024;
 
 bool setup_perm(const TileArgs& t, int elem, PermArgs& g) {
@@ -1169,8 +1171,8 @@ bool choose_shared(const Fused& f, int elem, const hptt_options_t& opt, TileArgs
 // LDS of a tile is 1/200 of the tensor, so that the CUs have one each (0.3-0.5
 // MB: 4.2-5.4 us, against 7.1-10.6 with 20 KB tiles).  Above that, HBM binds:
 //  - fp32 with beta == 0, runs of at least 1 KiB on both sides and two tiles
-//    per workgroup: 90-122 us -> 79-86 at 200 MB (kernel T 82% of the copy
-//    rate at best, kernel P 92%).  Shorter runs are 0-20% slower (2x565x30x1475:
+//    per workgroup: 0.84 of kernel T's time over 60 problems of 120 to 260 MB
+//    (0.62 to 1.08).  Shorter runs are 0-20% slower (2x565x30x1475:
 //    107 -> 126-148 us), fewer tiles leave the last turn of the workgroups
 //    partly empty (20-40 MB: 16.4 -> 18.1 us).
 //  - fp64 halves kernel T's index work per byte, and with beta != 0 twice the

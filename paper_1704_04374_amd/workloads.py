@@ -121,16 +121,26 @@ SUBTENSOR_WORKLOADS = [
 # perm [2, 0, 4, 1, 3]).
 #
 # And a 2-D fp32 transposition whose 32-element A runs start off the 128-byte
-# lines (A rows of 2193 elements), once with the quick plan (tiles dealt to
-# the XCDs 16 at a time) and once with the same tiles dealt one by one, round
-# robin: neighbouring tiles, which share A's boundary lines, then sit in
-# different XCDs' L2s.
+# lines (A rows of 2193 elements), once with kernel T's tiles (the block limit
+# keeps the plan with kernel T) dealt to the XCDs 16 at a time and once with the
+# same tiles dealt one by one, round robin: neighbouring tiles, which share A's
+# boundary lines, then sit in different XCDs' L2s.  The others are what the quick
+# plan runs of kernel M (the same problem, and an update of B), of kernel P and of
+# the flat walk.
 DIAGNOSTIC_WORKLOADS = [
     Workload("oneplane6d_24x20x320x24x18_f32", "f32", (24, 20, 320, 24, 18), (2, 0, 4, 1, 3),
              1.5, 0.0, 2, None, knobs=(("run_a", 96), ("run_b", 32))),
-    Workload("xcdgroups2d_2193x22800_f32", "f32", (2193, 22800), (1, 0), 1.0, 0.0, 9, None),
+    Workload("xcdgroups2d_2193x22800_f32", "f32", (2193, 22800), (1, 0), 1.0, 0.0, 9, None,
+             knobs=(("max_blocks", 1 << 30),)),
     Workload("roundrobin2d_2193x22800_f32", "f32", (2193, 22800), (1, 0), 1.0, 0.0, 9, None,
              knobs=(("xcd_group", 1), ("tile_order", 2))),
+    Workload("matrix2d_2193x22800_f32", "f32", (2193, 22800), (1, 0), 1.0, 0.0, 9, None),
+    Workload("matrix4d_427x110x3x355_f32", "f32", (427, 110, 3, 355), (3, 2, 1, 0), 1.0, 1.0, 9,
+             10),
+    Workload("perm4d_2925x1207x2x7_f32", "f32", (2925, 1207, 2, 7), (2, 0, 3, 1), 1.0, 0.0, 9,
+             None),
+    Workload("flat4d_75x100x11x606_f32", "f32", (75, 100, 11, 606), (0, 3, 2, 1), 1.0, 0.0, 9,
+             None),
 ]
 
 BY_NAME = {w.name: w for w in WORKLOADS + SUBTENSOR_WORKLOADS + DIAGNOSTIC_WORKLOADS}
