@@ -55,10 +55,27 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in ("kernel_body.h", "kernels.hip", "plan.cpp", "hptt_args.h", "device_mem.h",
               "tile_kernel.h", "tile_f32_fast.hip", "tile_f32_shifted.hip", "tile_f32_general.hip",
-              "tile_shared.hip", "tile_direct.hip", "tile_f64.hip"):
+              "tile_shared.hip", "tile_direct.hip", "tile_f64.hip", "matrix_body.h", "perm_body.h",
+              "tile_matrix.hip", "tile_perm.hip"):
         with open(os.path.join(ROOT, "paper_1704_04374_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
+
+
+# what the names of the transposition kernels hold
+TRANSPOSITIONS = ("tile_kernel", "matrix_kernel", "perm_kernel", "stream_kernel",
+                  "stream_flat_kernel", "axpby_kernel<")
+
+
+def kernel_class(plan) -> str:
+    """The kernel that a plan launches: its class, or the kernel that takes the
+    tile plan's or the row walk's place."""
+    text, info = plan.describe(), plan.info
+    for word, name in ((" matrix=", "matrix"), (" permute=", "perm")):
+        if word in text:
+            return name
+    return "stream_flat" if info["kernel"] == "stream" and info["flat_runs"] and not (
+        info["mode"] == "axpby" and info["run_b"] * info["elem_bytes"] > 320) else info["kernel"]
 
 
 def kernel_label(kernel_class: str) -> str:
@@ -220,7 +237,7 @@ def measure_workload(torch, hptt, w, steps, warmup, reps, flush_buf, sink, full:
     moved = w.moved_bytes
     S = w.tensor_bytes
     out = {"workload": w.name, "plan": plan.describe(), "plan_create_us": round(plan_us, 1),
-           "bytes_per_launch": moved, "buffer_sets": k, "kernel_class": plan.info["kernel"]}
+           "bytes_per_launch": moved, "buffer_sets": k, "kernel_class": kernel_class(plan)}
 
     stream = torch.cuda.current_stream().cuda_stream
     runs = [plan.launcher(As[j].data_ptr(), Bs[j].data_ptr(), stream) for j in range(k)]
@@ -390,8 +407,8 @@ def summarize_pmc(fetch_dir: str, write_dir: str, workload: str, command: str, o
         return names[0], statistics.median(vals)
 
     from paper_1704_04374_amd import hptt
-    cls = hptt.create_plan(w.perm, w.size_a, w.alpha, w.beta, w.dtype,
-                           **dict(w.knobs)).info["kernel"]
+    cls = kernel_class(hptt.create_plan(w.perm, w.size_a, w.alpha, w.beta, w.dtype,
+                                        **dict(w.knobs)))
     tk, tf = pick(fetch, kernel_label(cls))
     _, tw = pick(write, tk.split("(")[0])
     _, cf = pick(fetch, "copy_kernel")
@@ -442,8 +459,7 @@ def summarize_counters(dirs, workload: str, command: str, out_path: str):
             with open(path) as f:
                 for r in csv.DictReader(f):
                     name = r["Kernel_Name"]
-                    kind = ("transposition" if ("tile_kernel" in name or "stream_kernel" in name
-                                                or "axpby_kernel<" in name)
+                    kind = ("transposition" if any(k in name for k in TRANSPOSITIONS)
                             else "copy" if "copy_kernel" in name else None)
                     if kind:
                         acc.setdefault((kind, r["Counter_Name"]), []).append(
@@ -483,7 +499,7 @@ def summarize_trace(trace_dir: str, workload: str, command: str, out_path: str):
         name = r["Name"]
         avg = float(r["AverageNs"])
         nb = None
-        if "tile_kernel" in name or "stream_kernel" in name or "axpby_kernel<" in name:
+        if any(k in name for k in TRANSPOSITIONS):
             nb = w.moved_bytes
         elif "copy_kernel" in name:
             nb = 2 * w.tensor_bytes
@@ -673,8 +689,8 @@ def main():
         _w = _W[args.workload]
         import ctypes  # noqa: F401  (plan creation needs only the host half of the library)
         from paper_1704_04374_amd import hptt as _h
-        _cls = _h.create_plan(_w.perm, _w.size_a, _w.alpha, _w.beta, _w.dtype,
-                              **dict(_w.knobs)).info["kernel"]
+        _cls = kernel_class(_h.create_plan(_w.perm, _w.size_a, _w.alpha, _w.beta, _w.dtype,
+                                           **dict(_w.knobs)))
     if args.summarize_pmc:
         out = args.pmc_out or profile_path(_cls, args.workload, "pmc")
         summarize_pmc(*args.summarize_pmc, args.workload, args.pmc_command, out)
