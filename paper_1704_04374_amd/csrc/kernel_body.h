@@ -1013,9 +1013,9 @@ __host__ __device__ inline int64_t stream_row_a(const StreamArgs& g, uint32_t r)
 // (rows of 63 fp32 would otherwise move one element per access).  A workgroup
 // takes kFlatItems vectors per lane, consecutive in B; the A offsets of the
 // rows they lie in are split once per workgroup into an LDS table (MI355X,
-// rows of 75 fp32: splitting them in every lane, and reading the vectors that
-// cross into the next row element by element, took 135 VALU instructions and
-// 5 loads per 16-byte vector and wave).  A vector is read from A at any
+// rows of 75 fp32, per 16-byte vector and wave: 47 VALU instructions and 2
+// loads; splitting them in every lane, and reading the vectors that cross into
+// the next row element by element, took 135 and 5).  A vector is read from A at any
 // element boundary, as the last V elements of its row when it crosses into
 // the next, and then completed from the first V of that one.  Two vectors per
 // lane: on rows of 75, 213 and 498 fp32 one takes 77.4, 75.8 and 72.3 us, two

@@ -5,13 +5,14 @@
 // and kept in registers; a tile then costs its scalar base and, per vector,
 // the access and its LDS words.
 //
-// Kernel T's shared tiles are bound by issue, not by HBM: working these
-// numbers out anew in each tile takes 80-100 us of vector instructions out of
-// 107-126 us for 2 x 200 MB of fp32.  Over 60 drawn fp32 problems of 2 x 120 to
-// 2 x 260 MB 2.9-4.5 TB/s become 3.8-5.3 (0.84 of the time; the copy kernel moves
-// 6.7), and 7-12 us below 1 MB become 4-6.  One-element
-// LDS stores and loads, because a row's start in LDS and a B vector's elements
-// lie anywhere; the next tile's A is fetched while this one is written.
+// Kernel T's shared tiles are bound by issue, not by HBM: 2925x1207x2x7
+// [2,0,3,1] fp32 takes 38 M vector instructions, 62 of its 91 us at one per SIMD
+// and 4 cycles, most of them for these numbers; here 6.8 M and 81 us.  Over 60
+// drawn fp32 problems of 2 x 120 to 2 x 260 MB 2.9-4.5 TB/s become 3.8-5.3 (0.84
+// of the time; the copy kernel moves 6.7), and 7-12 us below 1 MB become 4-6.
+// One-element LDS stores and loads, because a row's start in LDS and a B
+// vector's elements lie anywhere; the next tile's A is fetched while this one is
+// written.
 #pragma once
 
 #include "kernel_body.h"

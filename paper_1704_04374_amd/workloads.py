@@ -125,8 +125,8 @@ SUBTENSOR_WORKLOADS = [
 # keeps the plan with kernel T) dealt to the XCDs 16 at a time and once with the
 # same tiles dealt one by one, round robin: neighbouring tiles, which share A's
 # boundary lines, then sit in different XCDs' L2s.  The others are what the quick
-# plan runs of kernel M (the same problem, and an update of B), of kernel P and of
-# the flat walk.
+# plan runs of kernel M (the same problem, and an update of B), of kernel P (with
+# kernel T's shared-run tiles for the same problem) and of the flat walk.
 DIAGNOSTIC_WORKLOADS = [
     Workload("oneplane6d_24x20x320x24x18_f32", "f32", (24, 20, 320, 24, 18), (2, 0, 4, 1, 3),
              1.5, 0.0, 2, None, knobs=(("run_a", 96), ("run_b", 32))),
@@ -139,6 +139,8 @@ DIAGNOSTIC_WORKLOADS = [
              10),
     Workload("perm4d_2925x1207x2x7_f32", "f32", (2925, 1207, 2, 7), (2, 0, 3, 1), 1.0, 0.0, 9,
              None),
+    Workload("shared4d_2925x1207x2x7_f32", "f32", (2925, 1207, 2, 7), (2, 0, 3, 1), 1.0, 0.0, 9,
+             None, knobs=(("max_blocks", 1 << 30),)),
     Workload("flat4d_75x100x11x606_f32", "f32", (75, 100, 11, 606), (0, 3, 2, 1), 1.0, 0.0, 9,
              None),
 ]
