@@ -193,3 +193,30 @@ def test_hints_of_every_plan_have_a_kernel():
         assert hints != 3 or (shear == 0 and cols * (4 if dtype == "f32" else 8) % 128 == 0)
         seen.add(hints)
     assert seen == {0, 1, 3}
+
+
+@pytest.mark.parametrize("size,perm,dtype,fits", [
+    ((32771, 32749), (1, 0), "f32", True),          # 2^32 - 2.1 M bytes
+    ((32771, 32771), (1, 0), "f32", False),
+    ((23167, 23161), (1, 0), "f64", True),
+    ((23171, 23173), (1, 0), "f64", False),
+    ((1021, 1009, 1033, 3), (1, 2, 0, 3), "f32", True),   # the offsets of one of three matrices
+    ((37, 5003, 5779), (2, 1, 0), "f32", True),
+])
+def test_largest_offsets(size, perm, dtype, fits):
+    """Matrices just below 2^32 bytes, whose offsets fill 32 bits: the first and
+    the last tile and a sample between; those above are kernel T's."""
+    import re
+
+    from emulator import emu
+    for beta in (0.0, 1.0):
+        p = emu.plan(perm, size, 1.0, beta, dtype)
+        m = re.search(r"matrix=.* tiles=(\d+)", p.describe())
+        assert bool(m) == fits, p.describe()
+        if not m:
+            continue
+        tiles = int(m.group(1))
+        for stride in (max(1, tiles - 1), tiles // 211, tiles // 97):
+            for mis in (0, 1):
+                err, msg, _ = emu.run(p, block_stride=stride, mis_b=mis)
+                assert err == 0, f"{p.describe()}: {msg}"
