@@ -128,12 +128,14 @@ __host__ __device__ __forceinline__ void direct_column(const DirectArgs& g, cons
     if (d.y + c < g.y.total) group_offsets(g.y, uint32_t(d.y + c), inQ, inC);
 }
 
-// Offsets of slice kb's position j; beyond the contraction those of its first
-// element, whose products are left out.
+// Offsets of slice kb's position j, to *inP and *inQ; beyond the contraction those
+// of its first element, whose products are left out.
 __host__ __device__ __forceinline__ void direct_position(const DirectArgs& g, int slice, int kb,
-                                                         int j, uint32_t& inP, uint32_t& inQ) {
-    inP = inQ = 0;
-    if (kb * slice + j < g.k.total) group_offsets(g.k, uint32_t(kb * slice + j), inP, inQ);
+                                                         int j, uint32_t* inP, uint32_t* inQ) {
+    uint32_t p = 0, q = 0;
+    if (kb * slice + j < g.k.total) group_offsets(g.k, uint32_t(kb * slice + j), p, q);
+    *inP = p;
+    *inQ = q;
 }
 
 // A block's tables, one entry per thread: rows, columns, and slice 0 (which
@@ -149,7 +151,7 @@ __host__ __device__ __forceinline__ void direct_tables(const DirectArgs& g, cons
     if (tid < kBM) direct_row(g, d, tid, rowP[tid], rowC[tid]);
     else if (tid < kBM + kBN) direct_column(g, d, tid - kBM, colQ[tid - kBM], colC[tid - kBM]);
     else if (tid < kBM + kBN + SLICE)
-        direct_position(g, SLICE, 0, tid - kBM - kBN, kP[tid - kBM - kBN], kQ[tid - kBM - kBN]);
+        direct_position(g, SLICE, 0, tid - kBM - kBN, &kP[tid - kBM - kBN], &kQ[tid - kBM - kBN]);
 }
 
 // Staging slot s of P: row, slice position and place in a slice's LDS row.

@@ -44,16 +44,18 @@ __device__ __forceinline__ T at_bytes(const T* base, uint32_t off) {
 // One 128 x 64 block of C per workgroup.  Per slice each thread holds the next
 // slice's elements in registers while the waves multiply the staged one (one
 // LDS buffer, two barriers); offsets come from LDS tables computed once per
-// block, the contracted positions' per slice.  fp64 takes slices of 8 and both
-// types are held to 128 registers (4 waves per SIMD): against slices of 16 and
-// 3 waves, fp64 abcd = dbea.ec (64 contracted) 207 -> 175 us, abc = bda.dc 96
-// -> 87; a long contraction, bound by the chain of slices, loses 3 to 9 %.
+// block, the contracted positions' per slice.  fp64 takes slices of 8 and is held
+// to 128 registers (4 waves per SIMD): against slices of 16 and 3 waves, abcd =
+// dbea.ec (64 contracted) 207 -> 175 us, abc = bda.dc 96 -> 87; a long
+// contraction, bound by the chain of slices, loses 3 to 9 %.  fp32 is held to 96
+// (5 waves): with 98, at 4 waves, many small products took up to 1.19x as long
+// (cdahb = eghaf.fcbdehg, 213 batches of 341 x 12 x 10: 10.3 -> 12.3 us).
 // With few contracted elements the kernel is bound by the traffic of C: fp64
 // abcde = efbad.cf (340 MB of tensors, 2.0 GFLOP) takes 73 us, 4.7 TB/s,
 // where transposition - GEMM - transposition moves 1.0 GB in 235 us.  Lanes
 // store 16 rows of 4 columns at a time, 128-byte (fp64) pieces of C.
 template <typename T, bool BETA, bool NT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void direct_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 5))) void direct_kernel(
     const T* __restrict__ P0,
                                                         const T* __restrict__ Q0,
                                                         T* __restrict__ C0, const DirectArgs g,
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int u = 0; u < kSlotsQ; ++u) ldsQ[toQ[u] & 0xffff] = vq[u];
         const bool more = kb + 1 < slices;
         const int next = (kb + 1) & 1;
-        if (more && tid < kBK) direct_position(g, kBK, kb + 1, tid, kP[next][tid], kQ[next][tid]);
+        if (more && tid < kBK) direct_position(g, kBK, kb + 1, tid, &kP[next][tid], &kQ[next][tid]);
         __syncthreads();
         if (more) fetch(kb + 1);
 #pragma unroll

@@ -110,7 +110,7 @@ int64_t emulate(const char* mA, const char* mB, const char* mC, const int64_t* e
             const int next = (kb + 1) & 1;
             if (more) {
                 for (int j = 0; j < kBK; ++j)
-                    direct_position(g, kBK, kb + 1, j, kP[next][j], kQ[next][j]);
+                    direct_position(g, kBK, kb + 1, j, &kP[next][j], &kQ[next][j]);
                 fetch(kb + 1, true);
                 fetch(kb + 1, false);
                 // stale from here on: the next entries go there
