@@ -140,7 +140,9 @@ bool use_direct(hptt_contraction_s* p) {
             const bool beta =
                 p->dtype == HPTT_FLOAT32 ? float(p->beta) != 0.f : p->beta != 0.0;
             return hptt::direct_us(p->dargs, elem, beta) <
-                   0.95 * hptt::transposed_us(p->dargs, elem, transposes, in.bytes_transposed);
+                   0.9 * hptt::transposed_us(in.gemm_m, in.gemm_n, in.gemm_k, in.batch, elem,
+                                              transposes, in.bytes_transposed,
+                                              beta && !in.transpose_c);
         }
     return false;
 }

@@ -192,9 +192,11 @@ bool plan_direct(const std::string& modesP, const std::string& modesQ, const std
                  const int64_t* ext, int elem, DirectArgs* g);
 
 // Estimated time in microseconds (MI355X) of the kernel on a planned problem,
-// and of `transposes` transpositions of `bytesMoved` bytes in all around a GEMM.
+// and of `transposes` transpositions of `bytesMoved` bytes in all around a GEMM of
+// m x n x k, `batch` times, that reads its C or does not.
 double direct_us(const DirectArgs& g, int elem, bool beta);
-double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved);
+double transposed_us(double m, double n, double k, double batch, int elem, int transposes,
+                     double bytesMoved, bool readC);
 
 // In libhptt.so: a failed launch's error, for hptt_last_hip_error; and a plan
 // whose result is read next, so that nothing of it is stored non-temporally.

@@ -3,6 +3,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "contract_direct.h"
 
@@ -193,53 +194,56 @@ double spread(const DirectArgs& g, const int64_t* strides) {
 
 }  // namespace
 
-// The constants are fitted to 5,789 random contractions on MI355X (fp64 and
-// fp32, 2,405 of them with batch modes, 1,932 with beta = 1; tensors to 300 MB,
-// most read from memory): the estimate's logarithm is within 0.19 (one standard
-// deviation) of the measured one.  With the margin that use_direct asks for the
-// calls take 0.713 of transposition - GEMM - transposition on average; 46 of
-// them are more than 3 % slower than that, 23 more than 10 %, the worst 1.37x.
-// Without the spread of the batch modes, the read of C and the margin it was
-// 0.712, 131, 91 and up to 4.4x.
+// The constants are fitted to 5,789 random contractions on MI355X and, for what
+// large operands read again, 1,920 more (fp64 and fp32, 3,228 with batch modes,
+// 2,576 with beta = 1; tensors to 300 MB, most read from memory), each timed both
+// ways: the logarithms of both estimates are within 0.18 (one standard
+// deviation) of the measured ones.  With the margin that use_direct asks for the
+// calls take 0.714 of transposition - GEMM - transposition on average and 1.010 of
+// the faster of the two; 103 of the 7,709 are more than 3 % slower than that path,
+// 57 more than 10 %, the worst 1.62x.  With estimates that knew of neither the batch
+// modes' spread, nor the read of C, nor the GEMM's padding, and no margin, it was
+// 0.718 and 1.016; 199, 138 and up to 4.4x.
 double direct_us(const DirectArgs& g, int elem, bool beta) {
     const bool f64 = elem == 8;
     double P, Q, C;
     tensor_bytes(g, elem, &P, &Q, &C);
-    // runs of C below 64 bytes write parts of its lines
-    const int64_t run = run_c(g, elem);
-    if (run < 64) C *= run < 16 ? 4 : 64.0 / double(run);
-    if (beta) C *= 2.5;
+    // runs of C below 64 bytes write parts of its lines, at a greater cost where
+    // the lines have been read before
+    const double parts = std::min(4.0, std::max(1.0, 64.0 / double(run_c(g, elem)))) - 1;
+    const double out =
+        beta ? C * (2.5 + parts) : C + parts * (0.4 * C + 0.2 * std::max(0.0, C - 30e6));
     const int bk = direct_slice(elem);
     const double slices = (g.k.total + bk - 1) / bk;
     const double rows = double(g.tiles1.d) * g.tiles2.d * kBM;
     const double cols = (g.y.total + 15) / 16 * 16.0;  // products of 16 columns are left out
     const double flops = 2.0 * rows * cols * slices * bk * batches(g);
-    // what is read again: the other parts of lines that hold several batches,
-    // more so in a tensor beyond the L2 caches, and the operands by other blocks
-    const double sP = spread(g, g.sLP), sQ = spread(g, g.sLQ);
-    const double far = 8e6;
-    const double again = (sP - 1) * (0.3 * P + std::max(0.0, P - far)) +
-                         (sQ - 1) * (0.3 * Q + std::max(0.0, Q - far)) +
-                         0.13 * (sP * P * (g.tilesY.d - 1.0) +
-                                 sQ * Q * (double(g.tiles1.d) * g.tiles2.d - 1.0));
-    const double stream = overlap(flops / (f64 ? 78e6 : 140e6), (P + Q + C + again) / 5.8e6, 0.9);
+    // what is read again: the operands by other blocks, and the other parts of
+    // lines that hold several batches, the more of these the larger the tensor
+    const double ny = g.tilesY.d, nx = double(g.tiles1.d) * g.tiles2.d;
+    auto again = [](double bytes, double parts, double times) {
+        return (parts - 1) * (0.21 + bytes / 200e6) * bytes * std::pow(times, 0.6) +
+               0.25 * bytes * (times - 1);
+    };
+    const double moved = P + again(P, spread(g, g.sLP), ny) + Q + again(Q, spread(g, g.sLQ), nx);
+    const double stream = overlap(flops / (f64 ? 86e6 : 143e6), (moved + out) / 4.85e6, 0.84);
     // a block's slices follow each other; about 1024 blocks run at one time
     const double rounds = (g.numTiles + 1023) / 1024;
-    const double chain = rounds * (slices * (f64 ? 1.0 : 1.2) + (beta ? 2.0 : 0.0) + 0.9);
-    return 3.7 + overlap(stream, chain, 0.9);
+    const double chain = rounds * (slices * (f64 ? 1.0 : 1.2) + (beta ? 2.0 : 0.0) + 0.84);
+    return 3.8 + overlap(stream, chain, 0.84);
 }
 
-// (fitted to 16 benchmark contractions and, for the latencies of small ones, 55
-// random ones)
-double transposed_us(const DirectArgs& g, int elem, int transposes, double bytesMoved) {
-    double P, Q, C;
-    tensor_bytes(g, elem, &P, &Q, &C);
-    const double flops =
-        2.0 * g.x1.total * double(g.x2.total) * g.y.total * double(g.k.total) * batches(g);
-    // a long contraction is a chain for the GEMM too
-    const double k = g.k.total < 700 ? g.k.total : 700;
-    return 7.6 + 2.3 * transposes + bytesMoved / 4.5e6 + k * (elem == 8 ? 0.022 : 0.013) +
-           overlap(flops / (elem == 8 ? 58e6 : 125e6), (P + Q + C) / 4e6, 0.3);
+// The GEMM works on padded tiles, several rounds of them where it has many
+// batches, and a long contraction is a chain for it too.
+double transposed_us(double m, double n, double k, double batch, int elem, int transposes,
+                     double bytesMoved, bool readC) {
+    const bool f64 = elem == 8;
+    const double tiles = std::ceil(m / 64) * std::ceil(n / 32) * batch;
+    const double flops = 2.0 * tiles * 64 * 32 * k;
+    const double bytes = (m * k + n * k + m * n * (readC ? 2 : 1)) * batch * elem;
+    const double gemm = overlap(overlap(flops / (f64 ? 98e6 : 110e6), bytes / 8.5e6, 1.1),
+                                std::min(k, 700.0) * (f64 ? 0.029 : 0.0063), 1.1);
+    return 6.6 + 3.0 * transposes + bytesMoved / 5.7e6 + gemm + 0.7 * std::ceil(tiles / 256);
 }
 
 }  // namespace hptt

@@ -216,6 +216,10 @@ DIRECT_CHOICES = [
     ("abcd=aebf*dfce", dict(a=72, b=72, c=72, d=72, e=4, f=4), "f64", 0.0, True),      # 50, 62
     ("abcde=efbad*cf", dict(a=24, b=24, c=96, d=24, e=24, f=32), "f64", 1.0, True),    # 153, 269
     ("abcd=dbea*ec", dict(a=96, b=64, c=96, d=64, e=64), "f32", 1.0, True),            # 157, 260
+    # short runs of a C that is read, and many small products (tiles of the GEMM
+    # that are mostly padding)
+    ("adcb=afeb*ecfd", dict(a=2, b=248, c=79, d=42, e=4, f=2), "f64", 1.0, True),      # 12, 30
+    ("becaf=aefd*fbced", dict(a=6, b=912, c=4, d=7, e=3, f=42), "f32", 0.0, True),     # 39, 136
     ("ab=acd*dbc", dict(a=2048, b=2048, c=64, d=64), "f64", 0.0, False),               # 801, 543
 ]
 
