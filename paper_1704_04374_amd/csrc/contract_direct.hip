@@ -55,11 +55,10 @@ __device__ __forceinline__ T at_bytes(const T* base, uint32_t off) {
 // where transposition - GEMM - transposition moves 1.0 GB in 235 us.  Lanes
 // store 16 rows of 4 columns at a time, 128-byte (fp64) pieces of C.
 template <typename T, bool BETA, bool NT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 5))) void direct_kernel(
-    const T* __restrict__ P0,
-                                                        const T* __restrict__ Q0,
-                                                        T* __restrict__ C0, const DirectArgs g,
-                                                        T alpha, T beta) {
+__global__ __launch_bounds__(kBlock)
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 ? 4 : 5))) void direct_kernel(
+        const T* __restrict__ P0, const T* __restrict__ Q0, T* __restrict__ C0, const DirectArgs g,
+        T alpha, T beta) {
     typedef typename Mfma<T>::acc acc;
     constexpr int kBK = direct_slice(sizeof(T));
     constexpr int kSlotsP = kBM * kBK / kBlock;  // elements a thread stages per slice
